@@ -13,33 +13,44 @@
 // heads and the position embedding fused into the producing kernel.
 //
 // Work decomposition
-//   * one workgroup = 8 waves = one 256 (m) x 256 (n) tile of Y; wave w owns
-//     the 64 rows 64 (w >> 1) + [0, 64) and the 128 columns 128 (w & 1) +
-//     [0, 128) of the tile, as 2 x 4 tiles of 32 x 32;
+//   * one workgroup computes a BM (m) x BN (n) tile of Y: 256 x 256 with 8
+//     waves where that fills the CUs, down to 64 x 64 with 4 (pick_tile); the
+//     waves share it as WM x WN rectangles of 32 x 32 MFMA tiles.  Whatever
+//     the tile, every element sums its products in the order of k, so all
+//     tiles give the same bits;
 //   * both operands are K-contiguous rows, which is the operand layout of
 //     v_mfma_f32_32x32x16_bf16 (8 consecutive k per lane), so neither needs a
 //     transpose: the MFMA computes Y^T tiles, D[n][m] = sum_k W[n][k] X[m][k],
 //     with W rows as the A operand and X rows as the B operand.  Each lane
 //     then holds one row m and, per 32 x 32 tile, 4 runs of 4 consecutive
-//     columns n: whole rotation pairs; bf16 output goes through LDS so that
+//     columns n: whole rotation pairs; the output goes through LDS so that
 //     it leaves as 16-byte stores covering whole row segments;
-//   * k advances in blocks of 64: the 256 x 64 blocks of X and W are staged
-//     global -> registers -> LDS (rows padded to 144 bytes, so 16 lanes
-//     reading 16 rows hit 16 disjoint groups of 4 banks), double-buffered in
-//     LDS, with two register sets so that each block's global loads are
-//     issued two k-blocks before its MFMAs; every operand read from LDS feeds
-//     2 (W) or 4 (X) MFMAs;
+//   * k advances in stages of 128 bytes per row (64 columns of bf16, 32 of
+//     fp32), which go from global memory straight into one of ST LDS buffers
+//     (buffer_load_dwordx4 ... lds) a stage or more ahead; fp32 operands are
+//     rounded to bf16 when they are read from LDS;
+//   * one barrier per stage, placed where the operands of the stage's last
+//     k-step are already in registers: it frees that stage's buffer and hands
+//     over the next one, and the MFMAs behind it need neither.  Before, the
+//     operand reads followed the barrier and the blocks passed through
+//     registers: 8192 x 8192 x 8192 took 925 us (1188 TFLOP/s), 56160 x 1920 x
+//     5120 1056, 56160 x 5120 x 640 406; on the same card now 793, 923 and
+//     345.  What bounds it now: the power limit (1.7 GHz with the matrix
+//     cores 75 % busy; without any load it would run 8 % faster, an MFMA loop
+//     with the same LDS reads on random operands reaches 1710 TFLOP/s);
 //   * tiles are ordered in groups of 8 row tiles (all column tiles of a group
-//     before the next group); the grid holds one persistent workgroup per CU,
-//     each round of the grid takes the next G tiles of that order, and the 8
-//     XCDs each take a contiguous range of a round, so the 32 workgroups
-//     resident on an XCD share 8 X panels and 4 W panels through its L2;
-//   * a workgroup's tiles form one stream of k-blocks, so the next tile's
-//     first blocks load during the current tile's last ones and its epilogue.
+//     before the next group); workgroups are persistent, each round of the
+//     grid takes the next G tiles of that order, and the 8 XCDs each take a
+//     contiguous range of a round, so the 32 workgroups resident on an XCD
+//     share 8 X panels and 4 W panels through its L2;
+//   * a workgroup's tiles form one stream of stages, so the next tile's first
+//     stages load during the current tile's last ones and its epilogue.
 //
 // Tails: rows past M or N are read through buffer resources bounded by the
 // last row, so they read as zeros; rows past M and columns past N are not
 // stored.  K must be a multiple of 64 and N of 8 (checked by the caller).
+#include <type_traits>
+
 #include "attention_tiles.h"
 #include "hcms_internal.h"
 
@@ -50,22 +61,22 @@ using namespace tiles;
 
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 
-constexpr int kBM = 256, kBN = 256, kBK = 64;
-#ifndef HCMS_LINEAR_WAVES
-#define HCMS_LINEAR_WAVES 8
-#endif
-constexpr int kWaves = HCMS_LINEAR_WAVES;    // 8: 64 x 128 per wave; 4: 128 x 128 per wave
-constexpr int kThreads = 64 * kWaves;
-constexpr int kWavesN = 2;                   // waves across the 256 columns
-constexpr int kWavesM = kWaves / kWavesN;    // waves across the 256 rows
-constexpr int kMT = kBM / kWavesM / 32;      // 32-row tiles per wave
-constexpr int kNT = kBN / kWavesN / 32;      // 32-column tiles per wave
-constexpr int kRow = kBK + 8;            // LDS row stride, elements (144 bytes)
-constexpr int kTile = 256 * kRow;        // one staged 256 x 64 block, elements
 constexpr int kGroupM = 8;               // row tiles per group of the tile order
-constexpr int kPersistK = 1024;          // longest K run by persistent workgroups
-constexpr int kPass = 256 * (kBK / 8) / kThreads;  // 16-byte chunks per thread per block
-constexpr int kRowsPerPass = kThreads / 8;
+
+// One workgroup's tile: BM rows of X by BN rows of W, WM x WN waves, ST stages
+// of LDS.  A stage holds 128 bytes of every row: kBK columns.
+template <int BM_, int BN_, int WM_, int WN_, int ST_, int PER_CU_>
+struct Tile {
+    static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, ST = ST_, PER_CU = PER_CU_;
+    static constexpr int W = WM * WN, THREADS = 64 * W;
+    static constexpr int MT = BM / WM / 32, NT = BN / WN / 32;   // 32 x 32 tiles per wave
+    static constexpr int XL = BM / 8 / W, WL = BN / 8 / W;       // loads per wave and stage
+    static constexpr int STAGE_B = (BM + BN) * 128;
+    static constexpr int OUT_B = 4096;                           // output staging per wave
+    static constexpr int LDS_B = ST * STAGE_B + W * OUT_B;
+    static_assert(XL * 8 * W == BM && WL * 8 * W == BN && W % 2 == 0, "whole loads per wave");
+    static_assert(LDS_B * PER_CU <= 160 * 1024 && ST >= 2, "LDS of a CU");
+};
 
 // Arguments of the QKV epilogue: destinations, and the rotation (table NULL:
 // no rotation).  table holds (cos, sin) pairs; axis a, coordinate c, pair i'
@@ -77,6 +88,8 @@ struct QkvOut {
     int H, d;
     RopeAxes ax;
 };
+template <typename T>
+using QkvArgs = __attribute__((address_space(4))) const QkvOut<T>;
 
 // Resource over [base, base + min(bytes, 2^32 - 1)).
 __device__ inline __amdgpu_buffer_rsrc_t span_rsrc(const void *base, int64_t bytes) {
@@ -85,91 +98,142 @@ __device__ inline __amdgpu_buffer_rsrc_t span_rsrc(const void *base, int64_t byt
                                              static_cast<int>(static_cast<uint32_t>(n)), 0x00020000);
 }
 
-// load8 with the byte offset split into a per-lane part and a scalar part
-// (the buffer range check covers both).
-template <typename T>
-__device__ inline u32x4 load8s(__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff);
-template <>
-__device__ inline u32x4 load8s<__bf16>(__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff) {
-    return __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0);
+// Output of one wave's MT x NT tiles at rows mb .., columns nb .. of Y.  Lane
+// (li, g) holds token mb + 32 mt + li and, per 32 x 32 tile, runs of 4
+// consecutive features 8 rb + 4 g.  Runs of 8 bytes, 32 rows apart, coalesce
+// badly, so the wave passes its part through a private 4 KiB of LDS, 32 tokens
+// by 128 bytes at a time, and stores whole 128-byte row segments, 16 bytes per
+// lane.  Chunk c of staged row r sits at position c ^ (r % 8).
+template <typename T, bool QKV, typename C>
+__device__ inline void store_tile(f32x16 (&acc)[C::NT][C::MT], char *stage, T *y, QkvArgs<T> *qp,
+                                  int mb, int nb, int M, int N, int lane) {
+    constexpr int MT = C::MT, NT = C::NT;
+    constexpr int kSeg = sizeof(T) == 2 ? (NT % 2 == 0 ? 2 : 1) : 1;   // 32-column tiles per segment
+    constexpr int kChunks = kSeg * 32 * sizeof(T) / 16;                // 16-byte chunks per staged row
+    constexpr int kRows = 64 / kChunks;                                // rows per store instruction
+    const int li = lane & 31, g = lane >> 5;
+    const int hd = qp->H * qp->d;
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+        int tab_row[kRopeMaxAxes] = {};
+        // The head element of the next 8 aligned columns.  Opaque, so that the
+        // compiler steps it instead of keeping all of a row's in registers.
+        int e8 = 0, n8 = 0;
+        if constexpr (QKV) {
+            n8 = nb;
+            asm volatile("" : "+s"(n8));
+            e8 = n8 % qp->d;
+            // Per grid axis, the table entry of pair 0 of the axis at the
+            // token's coordinate.
+            if (qp->table != nullptr) {
+                int rest = min(mb + mt * 32 + li, M - 1);
+                for (int a = qp->ax.n_axes - 1; a >= 0; --a) {
+                    const int cc = rest % qp->ax.grid[a];
+                    rest /= qp->ax.grid[a];
+                    tab_row[a] = qp->ax.tab_off[a] + cc * qp->ax.pairs[a] - qp->ax.pair_start[a];
+                }
+            }
+        }
+#pragma unroll
+        for (int sg = 0; sg < NT / kSeg; ++sg) {
+#pragma unroll
+            for (int h = 0; h < kSeg; ++h)
+#pragma unroll
+                for (int rb = 0; rb < 4; ++rb) {
+                    const f32x16 &t = acc[sg * kSeg + h][mt];
+                    f32x4 v = {t[rb * 4 + 0], t[rb * 4 + 1], t[rb * 4 + 2], t[rb * 4 + 3]};
+                    if constexpr (QKV) {
+                        // Features of 8 aligned columns share q / k / v and
+                        // head (N, H d and d are multiples of 8), the same
+                        // for the whole wave.
+                        if (qp->table != nullptr && n8 < 2 * hd) {
+                            const int e = e8 + g * 4;
+#pragma unroll
+                            for (int q2 = 0; q2 < 2; ++q2) {
+                                const int p = e / 2 + q2;
+                                int row = tab_row[0];
+#pragma unroll
+                                for (int a = 1; a < kRopeMaxAxes; ++a)
+                                    if (a < qp->ax.n_axes && p >= qp->ax.pair_start[a]) row = tab_row[a];
+                                const f32x2 cs = *reinterpret_cast<const f32x2 *>(qp->table + 2 * (row + p));
+                                const float x0 = v[2 * q2], x1 = v[2 * q2 + 1];
+                                v[2 * q2] = __builtin_fmaf(x0, cs[0], -(x1 * cs[1]));
+                                v[2 * q2 + 1] = __builtin_fmaf(x0, cs[1], x1 * cs[0]);
+                            }
+                        }
+                        n8 += 8;
+                        e8 = e8 + 8 == qp->d ? 0 : e8 + 8;
+                        asm volatile("" : "+s"(n8), "+s"(e8));
+                    }
+                    if constexpr (sizeof(T) == 2) {
+                        const int c = h * 4 + rb;
+                        *reinterpret_cast<bf16x4 *>(stage + li * kChunks * 16 +
+                                                    ((c ^ (li & (kChunks - 1))) << 4) + g * 8) =
+                            __builtin_convertvector(v, bf16x4);
+                    } else {
+                        const int c = rb * 2 + g;
+                        *reinterpret_cast<f32x4 *>(stage + li * kChunks * 16 + ((c ^ (li & (kChunks - 1))) << 4)) = v;
+                    }
+                }
+            // The lane's chunk of each staged row: 16 / sizeof(T) features.
+            const int ch = lane & (kChunks - 1);
+            const int n = nb + sg * kSeg * 32 + ch * (16 / static_cast<int>(sizeof(T)));
+            T *col;
+            int64_t ld;
+            if constexpr (QKV) {
+                const int z = n >= 2 * hd ? 2 : n >= hd ? 1 : 0;
+                col = qp->dst[z] + (n - z * hd);
+                ld = hd;
+            } else {
+                col = y + n;
+                ld = N;
+            }
+            u32x4 o[32 / kRows];
+#pragma unroll
+            for (int q = 0; q < 32 / kRows; ++q) {
+                const int row = q * kRows + lane / kChunks;
+                o[q] = *reinterpret_cast<const u32x4 *>(stage + row * kChunks * 16 + ((ch ^ (row & (kChunks - 1))) << 4));
+            }
+#pragma unroll
+            for (int q = 0; q < 32 / kRows; ++q) {
+                const int mm = mb + mt * 32 + q * kRows + lane / kChunks;
+                if (mm < M && n < N) *reinterpret_cast<u32x4 *>(col + static_cast<int64_t>(mm) * ld) = o[q];
+            }
+        }
+    }
 }
-template <>
-__device__ inline u32x4 load8s<float>(__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff) {
-    const f32x4 a = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0));
-    const f32x4 b = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, voff + 16, soff, 0));
+
+// Operand of k-step ks, 8 consecutive k of one row, from a staged row (128
+// bytes, 16-byte chunk c at position c ^ swizzle); `off` is the lane's offset
+// of k-step 0.  fp32 in LDS takes two chunks and is rounded to bf16.
+__device__ inline bf16x8 operand(const char *p, unsigned off, int ks, const __bf16 *) {
+    return *reinterpret_cast<const bf16x8 *>(p + (off ^ (ks << 5)));
+}
+__device__ inline bf16x8 operand(const char *p, unsigned off, int ks, const float *) {
+    const f32x4 a = *reinterpret_cast<const f32x4 *>(p + (off ^ (ks << 6)));
+    const f32x4 b = *reinterpret_cast<const f32x4 *>(p + (off ^ (ks << 6) ^ 16));
     const f32x8 x = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
-    return __builtin_bit_cast(u32x4, __builtin_convertvector(x, bf16x8));
+    return __builtin_convertvector(x, bf16x8);
 }
 
-// Global -> register staging of the 256 x 64 blocks of X and W at column k0.
-// Thread tid moves chunk tid % 8 (8 elements) of rows tid / 8 + kRowsPerPass p:
-// a per-lane offset fixed for the whole launch (row and chunk, the same for X
-// and W) plus the block's column in the scalar offset, so the k-loop computes
-// no addresses (temporaries written there made the compiler wait for the
-// loads in flight on every step).
-template <typename T>
-__device__ inline void stage_offsets(unsigned (&voff)[kPass], unsigned row_bytes, int tid) {
-#pragma unroll
-    for (int p = 0; p < kPass; ++p)
-        voff[p] = static_cast<unsigned>(tid / 8 + kRowsPerPass * p) * row_bytes + (tid & 7) * 8 * sizeof(T);
-}
-template <typename T>
-struct Stager {
-    u32x4 xr[kPass], wr[kPass];
-    __device__ void load(__amdgpu_buffer_rsrc_t xs, __amdgpu_buffer_rsrc_t ws,
-                         const unsigned (&voff)[kPass], int k0) {
-        const unsigned soff = static_cast<unsigned>(k0) * sizeof(T);
-#pragma unroll
-        for (int p = 0; p < kPass; ++p) {
-            xr[p] = load8s<T>(xs, voff[p], soff);
-            wr[p] = load8s<T>(ws, voff[p], soff);
-        }
-    }
-    __device__ void store(__bf16 *xt, __bf16 *wt, int tid) const {
-#pragma unroll
-        for (int p = 0; p < kPass; ++p) {
-            const int e = (tid / 8 + kRowsPerPass * p) * kRow + (tid & 7) * 8;
-            *reinterpret_cast<u32x4 *>(xt + e) = xr[p];
-            *reinterpret_cast<u32x4 *>(wt + e) = wr[p];
-        }
-    }
-};
+template <typename T, bool QKV, typename C>
+__global__ __launch_bounds__(C::THREADS, C::PER_CU *C::W / 4) void linear_kernel(
+    QkvOut<T> qo, const T *__restrict__ x, const T *__restrict__ w, T *__restrict__ y, int M, int N,
+    int K, int tiles_m, int tiles_n) {
+    constexpr int MT = C::MT, NT = C::NT, ST = C::ST, W = C::W;
+    // fp32 storage on the tiles with two stages: through registers, rounded
+    // to bf16 on the way into LDS, so that a stage holds 64 columns and twice
+    // as many bytes are in flight as the buffers could take; from HBM, whose
+    // latency a stage of 32 columns does not cover, 4096 x 4096 x 8192 took
+    // 471 us without it.
+    constexpr bool kReg = sizeof(T) == 4 && ST == 2;
+    using L = std::conditional_t<kReg, __bf16, T>;   // element type in LDS
+    constexpr int kBK = 128 / sizeof(L);   // columns per stage
+    constexpr int KS = kBK / 16;           // MFMA k-steps per stage
+    constexpr int LPW = C::XL + C::WL;     // loads per wave and stage
+    constexpr int kHalf = kReg ? LPW : (LPW + 1) / 2;   // of them right behind the barrier
+    __shared__ __attribute__((aligned(1024))) char lds[C::LDS_B];
 
-// Scheduling hint for one k-block: the operand reads of k-step ks + 1 and,
-// when the LDS stores of the next block follow the MFMAs, those stores run
-// between the MFMAs of k-step ks.
-template <bool kStores>
-__device__ inline void interleave_k_block() {
-    constexpr int kReads = kNT + kMT;            // operand reads per k-step
-    constexpr int kMfma = kNT * kMT;             // MFMAs per k-step
-    constexpr int kWrites = 2 * kPass;           // LDS stores per k-block
-    constexpr int kSteps = kBK / 16;
-    __builtin_amdgcn_sched_group_barrier(0x100, kReads, 0);  // DS read, k-step 0
-#pragma unroll
-    for (int ks = 0; ks < kSteps; ++ks) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            __builtin_amdgcn_sched_group_barrier(0x008, kMfma / 2, 0);           // MFMA
-            if (ks + 1 < kSteps) __builtin_amdgcn_sched_group_barrier(0x100, kReads / 2, 0);
-            if constexpr (kStores)
-                __builtin_amdgcn_sched_group_barrier(0x200, kWrites / (2 * kSteps), 0);  // DS write
-        }
-    }
-}
-
-template <typename T, bool QKV>
-__global__ __launch_bounds__(kThreads, 1) void linear_kernel(const T *__restrict__ x,
-                                                             const T *__restrict__ w,
-                                                             T *__restrict__ y, int M, int N, int K,
-                                                             int tiles_m, int tiles_n, QkvOut<T> qo) {
-    __shared__ __attribute__((aligned(16))) __bf16 xt[2][kTile];
-    __shared__ __attribute__((aligned(16))) __bf16 wt[2][kTile];
-
-    // Persistent tiles: the grid has at most one workgroup per CU, and round r
-    // of workgroup b computes tile r G + slot(b) of the grouped order (G = the
-    // grid size).  Workgroup b runs on XCD b % 8, and slot(b) gives each XCD a
-    // contiguous range of every round, so the workgroups resident on an XCD
-    // share a few X and W panels through its L2.
     const int G = gridDim.x, b = blockIdx.x;
     const int xcd = b & 7, per = G >> 3, rem = G & 7;
     const int slot = xcd * per + min(xcd, rem) + (b >> 3);
@@ -182,8 +246,8 @@ __global__ __launch_bounds__(kThreads, 1) void linear_kernel(const T *__restrict
         const int first_m = group * kGroupM;
         const int gm = min(tiles_m - first_m, kGroupM);
         const int in_group = L - group * kGroupM * tiles_n;
-        m0 = (first_m + in_group % gm) * kBM;
-        n0 = (in_group / gm) * kBN;
+        m0 = (first_m + in_group % gm) * C::BM;
+        n0 = (in_group / gm) * C::BN;
     };
 
     const unsigned row_bytes = static_cast<unsigned>(K) * sizeof(T);
@@ -194,228 +258,165 @@ __global__ __launch_bounds__(kThreads, 1) void linear_kernel(const T *__restrict
         return span_rsrc(w + static_cast<int64_t>(n0) * K, static_cast<int64_t>(N - n0) * row_bytes);
     };
 
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int li = lane & 31, g = lane >> 5;
-    const int wm = wave / kWavesN, wn = wave % kWavesN;
+    const int wm = wave / C::WN, wn = wave % C::WN;
 
-    f32x16 acc[kNT][kMT];  // [n tile][m tile]
-#pragma unroll
-    for (int nt = 0; nt < kNT; ++nt)
-#pragma unroll
-        for (int mt = 0; mt < kMT; ++mt) acc[nt][mt] = f32x16{};
+    // Load i of a wave brings rows 8 (i W + wave) + lane / 8 of the stage's X
+    // rows (then of its W rows), 16 bytes per lane; the lane at position
+    // lane % 8 of its row fetches chunk (lane % 8) ^ swizzle(row), swizzle(r) =
+    // (r / 2) % 8, so that 16 rows of one chunk lie in 16 different groups of
+    // 4 banks.
+    const unsigned voff = (8 * wave + (lane >> 3)) * row_bytes +
+                          (((lane & 7) ^ ((4 * wave + (lane >> 4)) & 7)) << (kReg ? 5 : 4));
+    const unsigned pass_bytes = 8 * W * row_bytes;
+    const unsigned lds0 = static_cast<unsigned>(reinterpret_cast<uintptr_t>(lds));
 
-    // ---- Epilogue: Y of the tile at (m0, n0) from the D^T accumulators,
-    // rounded to T.  Lane (li, g) holds token m = ... + li and, per 32 x 32
-    // tile, runs of 4 consecutive features n = ... + 8 rb + 4 g.
-    // Per grid axis, the table entry of pair 0 of the axis at token m's
-    // coordinate (QKV epilogue with a rotation only).
-    auto table_rows = [&](int m, int (&tab_row)[kRopeMaxAxes]) {
-        int rest = m;
-        for (int a = qo.ax.n_axes - 1; a >= 0; --a) {
-            const int cc = rest % qo.ax.grid[a];
-            rest /= qo.ax.grid[a];
-            tab_row[a] = qo.ax.tab_off[a] + cc * qo.ax.pairs[a] - qo.ax.pair_start[a];
-        }
-    };
-    // Features n .. n + 3 (n < N) of a token whose table rows are tab_row,
-    // rotated in place when they are query or key features.
-    auto rotate = [&](f32x4 &v, int n, const int (&tab_row)[kRopeMaxAxes]) {
-        const int hd = qo.H * qo.d;
-        const int z = n / hd, e = (n - z * hd) % qo.d;  // e a multiple of 4: pairs e/2, e/2 + 1
-        if (z >= 2) return;
-#pragma unroll
-        for (int q2 = 0; q2 < 2; ++q2) {
-            const int p = e / 2 + q2;
-            int a = 0;
-            while (a + 1 < qo.ax.n_axes && p >= qo.ax.pair_start[a + 1]) ++a;
-            const f32x2 cs = *reinterpret_cast<const f32x2 *>(qo.table + 2 * (tab_row[a] + p));
-            const float x0 = v[2 * q2], x1 = v[2 * q2 + 1];
-            v[2 * q2] = __builtin_fmaf(x0, cs[0], -(x1 * cs[1]));
-            v[2 * q2 + 1] = __builtin_fmaf(x0, cs[1], x1 * cs[0]);
-        }
-    };
-    // Where feature n of token m goes: Y, or the split q, k, v (8 consecutive
-    // features never straddle two of them: N and H d are multiples of 8).
-    auto dest = [&](int m, int n) -> T * {
-        if constexpr (QKV) {
-            const int hd = qo.H * qo.d;
-            const int z = n / hd;
-            return qo.dst[z] + static_cast<int64_t>(m) * hd + (n - z * hd);
-        } else {
-            return y + static_cast<int64_t>(m) * N + n;
-        }
-    };
-    // Direct stores of each lane's runs: fp32 storage (16 bytes a run) and the
-    // QKV epilogue, whose K = D reductions make its one tile per workgroup
-    // long, so that its stores cost little (staging them, with the rotation,
-    // ran 5 % slower).
-    auto store_direct = [&](int m0, int n0) {
-#pragma unroll
-        for (int mt = 0; mt < kMT; ++mt) {
-            const int m = m0 + wm * kMT * 32 + mt * 32 + li;
-            if (m >= M) continue;
-            int tab_row[kRopeMaxAxes] = {};
-            if (QKV && qo.table != nullptr) table_rows(m, tab_row);
-#pragma unroll
-            for (int nt = 0; nt < kNT; ++nt)
-#pragma unroll
-                for (int rb = 0; rb < 4; ++rb) {
-                    const int n = n0 + wn * kNT * 32 + nt * 32 + rb * 8 + g * 4;
-                    if (n >= N) continue;
-                    f32x4 v = {acc[nt][mt][rb * 4 + 0], acc[nt][mt][rb * 4 + 1],
-                               acc[nt][mt][rb * 4 + 2], acc[nt][mt][rb * 4 + 3]};
-                    if (QKV && qo.table != nullptr) rotate(v, n, tab_row);
-                    store4(dest(m, n), v);
-                }
-        }
-    };
-    // Plain epilogue, bf16 storage: runs of 8 bytes, 32 rows apart, coalesce
-    // badly (the output projection, K = H d = 640, lost a fifth of its time
-    // to them), so each wave
-    // transposes its 64 x 128 part through LDS, 32 tokens at a time, in a
-    // private 32 x 264-byte region of the buffer the tile's last k-block left
-    // free, and stores whole 256-byte row segments, 16 bytes per lane.
-    constexpr int kStRow = 128 * 2 + 8;  // bytes per staged row, 8 of them padding
-    static_assert(4 * 32 * kStRow <= kTile * 2 && kNT * 32 == 128, "staging fits one buffer");
-    auto store_staged = [&](int m0, int n0, char *stage) {
-#pragma unroll
-        for (int mt = 0; mt < kMT; ++mt) {
-#pragma unroll
-            for (int nt = 0; nt < kNT; ++nt)
-#pragma unroll
-                for (int rb = 0; rb < 4; ++rb) {
-                    const int c = nt * 32 + rb * 8 + g * 4;
-                    const f32x4 v = {acc[nt][mt][rb * 4 + 0], acc[nt][mt][rb * 4 + 1],
-                                     acc[nt][mt][rb * 4 + 2], acc[nt][mt][rb * 4 + 3]};
-                    *reinterpret_cast<bf16x4 *>(stage + li * kStRow + c * 2) =
-                        __builtin_convertvector(v, bf16x4);
-                }
-            const int c = (lane & 15) * 8;  // the lane's 8 features of a staged row
-            const int n = n0 + wn * kNT * 32 + c;
-#pragma unroll
-            for (int q0 = 0; q0 < 8; q0 += 4) {
-                u32x4 o[4];
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    o[q] = *reinterpret_cast<const u32x4 *>(stage + ((q0 + q) * 4 + (lane >> 4)) * kStRow + c * 2);
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int mm = m0 + wm * kMT * 32 + mt * 32 + (q0 + q) * 4 + (lane >> 4);
-                    if (mm < M && n < N)
-                        *reinterpret_cast<u32x4 *>(y + static_cast<int64_t>(mm) * N + n) = o[q];
-                }
-            }
-        }
-    };
-
-    // The k-blocks of the workgroup's tiles form one stream: NSETS register
-    // sets carry its blocks from global memory to LDS.  With two (bf16
-    // storage), stream block s is loaded into set s & 1 during block s - 2 and
-    // stored to LDS buffer s & 1 after block s - 1's MFMAs, so each load has
-    // two k-blocks to arrive, also across a tile boundary (the next tile's
-    // first blocks load during the current tile's last ones and its
-    // epilogue); with one (fp32 storage, whose loads need twice the
-    // registers) it is loaded during block s - 1.  The loads of blocks past
-    // the stream's end read within the last tile's resources (the next row's
-    // data or zeros) and the last store goes to a buffer nobody reads.
-    constexpr int NSETS = sizeof(T) == 2 ? 2 : 1;
-    const int nkb = K / kBK;
-    int ld_r = 0, ld_kb = 0;  // tile round and k-block of the next load
+    // The stages of the workgroup's tiles form one stream.  A stage past its
+    // end is loaded through empty resources: zeros into a buffer that nobody
+    // reads, so that every step issues the same number of loads.
+    const int nkb = K / kBK;   // K is a multiple of 64
+    int ld_r = 0, ld_kb = 0;
     int lm0, ln0;
     origin(0, lm0, ln0);
     __amdgpu_buffer_rsrc_t lxs = x_rsrc(lm0), lws = w_rsrc(ln0);
-    unsigned voff[kPass];
-    stage_offsets<T>(voff, row_bytes, tid);
-    auto load_next = [&](Stager<T> &st) {
-        st.load(lxs, lws, voff, ld_kb * kBK);
-        if (++ld_kb == nkb && ld_r + 1 < n_mine) {
-            ld_kb = 0;
-            ++ld_r;
+    // kReg: the fp32 values of the lane's chunk of every load, and their way
+    // into LDS.
+    f32x4 raw[kReg ? LPW : 1][2];
+    auto store_raw = [&](int buf) {
+#pragma unroll
+        for (int i = 0; i < LPW; ++i) {
+            const f32x8 v = __builtin_shufflevector(raw[i][0], raw[i][1], 0, 1, 2, 3, 4, 5, 6, 7);
+            *reinterpret_cast<bf16x8 *>(lds + buf * C::STAGE_B + (i * W + wave) * 1024 + lane * 16) =
+                __builtin_convertvector(v, bf16x8);
+        }
+    };
+    auto load_one = [&](int i, int buf) {
+        if constexpr (kReg) {
+            const __amdgpu_buffer_rsrc_t rs = i < C::XL ? lxs : lws;
+            const unsigned so = ld_kb * 256 + (i < C::XL ? i : i - C::XL) * pass_bytes;
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                raw[i][h] = __builtin_bit_cast(
+                    f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, voff + 16 * h, so, 0));
+            return;
+        }
+        const unsigned dst = lds0 + buf * C::STAGE_B + (i * W + wave) * 1024;
+        const unsigned soff = ld_kb * 128;
+        if (i < C::XL) load_lds(dst, lxs, voff, soff + i * pass_bytes);
+        else load_lds(dst, lws, voff, soff + (i - C::XL) * pass_bytes);
+    };
+    auto advance = [&]() {
+        if (++ld_kb < nkb) return;
+        ld_kb = 0;
+        if (++ld_r < n_mine) {
             origin(ld_r, lm0, ln0);
             lxs = x_rsrc(lm0);
             lws = w_rsrc(ln0);
+        } else {
+            lxs = span_rsrc(x, 0);
+            lws = span_rsrc(w, 0);
         }
     };
 
-    Stager<T> st[NSETS];
-    load_next(st[0]);
-    st[0].store(xt[0], wt[0], tid);
-    if (NSETS == 2) load_next(st[1 % NSETS]);
-    __syncthreads();
-    // With two register sets the next block's LDS stores go first, right
-    // after the barrier that ended every wave's reads of that buffer (its
-    // loads were issued a step earlier), then the MFMAs; the plain epilogue's
-    // k-loop keeps hints for the operand reads, the QKV one (one long tile per
-    // workgroup) leaves the order to the compiler, each measured fastest
-    // (about 2 % over the stores between the MFMAs).  With one set the block
-    // is loaded during this step and stored after the MFMAs.
-    constexpr bool kStoreFirst = NSETS == 2;
-    auto step = [&](int s, Stager<T> &ld, const Stager<T> &sto) {
-        load_next(ld);
-        if constexpr (kStoreFirst) sto.store(xt[(s + 1) & 1], wt[(s + 1) & 1], tid);
-        const __bf16 *xa = xt[s & 1] + (wm * kMT * 32 + li) * kRow + g * 8;
-        const __bf16 *wa = wt[s & 1] + (wn * kNT * 32 + li) * kRow + g * 8;
+    const unsigned rd = li * 128 + (((sizeof(L) == 2 ? g : 2 * g) ^ ((li >> 1) & 7)) << 4);
+    const char *const xrd = lds + wm * MT * 32 * 128;
+    const char *const wrd = lds + C::BM * 128 + wn * NT * 32 * 128;
+
+    f32x16 acc[NT][MT];
+    bf16x8 a[2][NT], bx[2][MT];
+    auto read_ops = [&](int set, int ks, int buf) {
+        const int base = buf * C::STAGE_B;
 #pragma unroll
-        for (int ks = 0; ks < kBK / 16; ++ks) {
-            bf16x8 a[kNT], bx[kMT];
+        for (int nt = 0; nt < NT; ++nt)
+            a[set][nt] = operand(wrd + base + nt * 32 * 128, rd, ks, static_cast<const L *>(nullptr));
 #pragma unroll
-            for (int nt = 0; nt < kNT; ++nt)
-                a[nt] = *reinterpret_cast<const bf16x8 *>(wa + nt * 32 * kRow + ks * 16);
-#pragma unroll
-            for (int mt = 0; mt < kMT; ++mt)
-                bx[mt] = *reinterpret_cast<const bf16x8 *>(xa + mt * 32 * kRow + ks * 16);
-#pragma unroll
-            for (int nt = 0; nt < kNT; ++nt)
-#pragma unroll
-                for (int mt = 0; mt < kMT; ++mt)
-                    acc[nt][mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[nt], bx[mt], acc[nt][mt],
-                                                                          0, 0, 0);
-        }
-        if constexpr (!kStoreFirst) {
-            sto.store(xt[(s + 1) & 1], wt[(s + 1) & 1], tid);
-            interleave_k_block<true>();
-        } else if constexpr (!QKV) {
-            interleave_k_block<false>();
-        }
-        __syncthreads();
+        for (int mt = 0; mt < MT; ++mt)
+            bx[set][mt] = operand(xrd + base + mt * 32 * 128, rd, ks, static_cast<const L *>(nullptr));
     };
-    // The k-blocks of one tile run in a loop of two steps without branches
-    // (register set and LDS buffer follow the stream index's parity), so the
-    // compiler's waits for the staged loads stay two blocks deep; the
-    // epilogue sits between tiles.
-    int s = 0;
+    auto mfma = [&](int set, int i) {
+        const int nt = i / MT, mt = i % MT;
+        acc[nt][mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[set][nt], bx[set][mt], acc[nt][mt], 0, 0, 0);
+    };
+
+#pragma unroll
+    for (int st = 0; st < ST; ++st) {
+        const int n = st < ST - 1 ? LPW : kHalf;
+#pragma unroll
+        for (int i = 0; i < LPW; ++i)
+            if (i < n) load_one(i, st);
+        if constexpr (kReg)
+            if (st < ST - 1) store_raw(st);
+        if (st < ST - 1) advance();
+    }
+    if constexpr (!kReg) wait_vm<(ST - 2) * LPW + kHalf>();
+    __syncthreads();
+    read_ops(0, 0, 0);
+
+    // MFMAs of operand set `set` with the loads l0 .. l1 - 1 into `into`.
+    auto phase = [&](int set, int l0, int l1, int into) {
+        constexpr int kMf = NT * MT;
+#pragma unroll
+        for (int i = 0; i < kMf; ++i) {
+            mfma(set, i);
+#pragma unroll
+            for (int l = 0; l < LPW; ++l)
+                if (l >= l0 && l < l1 && (l - l0) * kMf / (l1 - l0) == i) load_one(l, into);
+            if (l0 < l1) __builtin_amdgcn_sched_barrier(0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    int buf = 0, prev = ST - 1;
     for (int r = 0; r < n_mine; ++r) {
-        int kb = 0;
-        if (s & 1) {
-            step(s, st[1 % NSETS], st[0]);
-            ++s;
-            ++kb;
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) acc[nt][mt] = f32x16{};
+        // End the scalar loads of the code before the loop: one that could
+        // still be pending would turn the counted waits for the operand reads
+        // of the first k-step into waits for all of them (simm16: lgkmcnt 0,
+        // the others open).
+        __builtin_amdgcn_s_waitcnt(0xC07F);
+        for (int kb = 0; kb < nkb; ++kb) {
+            // All but the stage's last k-step, each beside the operand reads
+            // of the next; the first also issues the second half of the loads
+            // into the buffer that the step before freed (all of them right
+            // behind the barrier cost 2-3 %, thirds over three k-steps gained
+            // nothing more).
+#pragma unroll
+            for (int ks = 0; ks + 1 < KS; ++ks) {
+                read_ops((ks + 1) & 1, ks + 1, buf);
+                __builtin_amdgcn_sched_barrier(0);
+                phase(ks & 1, ks == 0 ? kHalf : LPW, LPW, prev);
+                if (ks == 0) advance();
+            }
+            if constexpr (kReg) store_raw(prev);
+            // The last k-step's operands are in registers: past this barrier
+            // the stage's buffer is free and the next stage is in LDS, so the
+            // last MFMAs run beside the first loads into the one and the first
+            // operand reads of the other, and the matrix cores do not wait for
+            // LDS after the barrier.
+            if constexpr (!kReg) wait_vm<(ST - 2) * LPW>();
+            __syncthreads();
+            const int next = buf + 1 == ST ? 0 : buf + 1;
+            read_ops(KS & 1, 0, next);
+            __builtin_amdgcn_sched_barrier(0);
+            phase((KS - 1) & 1, 0, kHalf, buf);
+            prev = buf;
+            buf = next;
         }
-        for (; kb + 1 < nkb; kb += 2, s += 2) {
-            step(s, st[0], st[1 % NSETS]);
-            step(s + 1, st[1 % NSETS], st[0]);
-        }
-        if (kb < nkb) {
-            step(s, st[0], st[1 % NSETS]);
-            ++s;
-        }
+        static_assert(KS % 2 == 0, "the first k-step's operands are in set 0");
         int m0, n0;
         origin(r, m0, n0);
-        if constexpr (sizeof(T) == 2 && !QKV) {
-            // The buffer of the tile's last block (stream block s - 1) is free
-            // until the next step stores block s + 1 there, after a barrier.
-            char *base = reinterpret_cast<char *>(wave < 4 ? xt[(s - 1) & 1] : wt[(s - 1) & 1]);
-            store_staged(m0, n0, base + (wave & 3) * 32 * kStRow);
-            __syncthreads();
-        } else {
-            store_direct(m0, n0);
-        }
-#pragma unroll
-        for (int nt = 0; nt < kNT; ++nt)
-#pragma unroll
-            for (int mt = 0; mt < kMT; ++mt) acc[nt][mt] = f32x16{};
+        // The QKV arguments are read from the kernel arguments here (qo is
+        // the first), so that they hold no registers in the k-loop.
+        QkvArgs<T> *qo_args = (QkvArgs<T> *)__builtin_amdgcn_kernarg_segment_ptr();
+        asm volatile("" : "+s"(qo_args));
+        store_tile<T, QKV, C>(acc, lds + ST * C::STAGE_B + wave * C::OUT_B, y, qo_args, m0 + wm * MT * 32,
+                              n0 + wn * NT * 32, M, N, lane);
     }
+    wait_vm<0>();   // no load into LDS is pending when the workgroup ends
 }
 
 // Rotation table: entry e of axis a (tab_off[a] <= e < tab_off[a] + grid[a] *
@@ -435,25 +436,98 @@ __global__ __launch_bounds__(256) void rope_table_kernel(float *table, RopeAxes 
     table[2 * e + 1] = static_cast<float>(sin(ang));
 }
 
+template <typename T, bool QKV, typename C>
+hipError_t launch_tile(const T *x, const T *w, T *y, int M, int N, int K, const QkvOut<T> &qo,
+                       int n_cu, hipStream_t stream) {
+    const int tiles_m = (M + C::BM - 1) / C::BM, tiles_n = (N + C::BN - 1) / C::BN;
+    const int64_t tiles = static_cast<int64_t>(tiles_m) * tiles_n;
+    if (tiles > 0x7fffffff) return hipErrorInvalidValue;
+    // Persistent workgroups, whose tiles stream without a pipeline refill: on
+    // 56160 x 1920 x 5120 923 us against 973 with one workgroup per tile, with
+    // K = 640 and N = 5120 345 against 370.  Two workgroups per CU overlap
+    // each other's refills and lose more to the fixed shares (8192 x 8192 x
+    // 4096 907 against 764), except when the reduction is short.
+    const int64_t slots = static_cast<int64_t>(n_cu) * C::PER_CU;
+    const bool persist = tiles > slots && (C::PER_CU == 1 || K <= 1024);
+    const int64_t blocks = persist ? slots : tiles;
+    if (blocks < 1) return hipErrorInvalidValue;
+    linear_kernel<T, QKV, C><<<static_cast<unsigned>(blocks), C::THREADS, 0, stream>>>(
+        qo, x, w, y, M, N, K, tiles_m, tiles_n);
+    return hipGetLastError();
+}
+
+// The tiles, and what a round of workgroups and a stage of 128 bytes of K
+// take on them, in us, measured (bf16; fp32 stages, as many bytes, take about
+// as long): a stage with every CU busy, at the clock the power limit leaves,
+// and with few of them busy, where the latency of the loads shows; and the
+// start and the epilogue of a round.  Larger tiles move fewer bytes per MFMA,
+// smaller ones keep more stages in flight and fill the CUs on smaller
+// outputs: on 8192 x 8192 x 4096 the first takes 396 us, the others 440, 438,
+// 495, 668 and 764; on 1560 x 5120 x 5120 99, 91, 86, 121, 123 and 140; on
+// 1560 x 1920 x 5120 97, 82, 81, 41, 56 and 53; on 500 x 2000 x 4096 73, 58,
+// 60, 28, 22 and 17.
+struct TileCost {
+    int bm, bn, per_cu;
+    double full, alone, fixed;
+};
+using TileA = Tile<256, 256, 4, 2, 2, 1>;
+using TileB = Tile<192, 256, 2, 4, 2, 1>;
+using TileC = Tile<256, 192, 4, 2, 2, 1>;
+using TileD = Tile<128, 128, 4, 2, 4, 1>;
+using TileE = Tile<64, 128, 2, 2, 4, 1>;
+using TileF = Tile<64, 64, 2, 2, 4, 2>;
+constexpr TileCost kTiles[] = {{256, 256, 1, 1.50, 0.99, 5.0}, {192, 256, 1, 1.18, 0.82, 4.5},
+                               {256, 192, 1, 1.18, 0.82, 4.5}, {128, 128, 1, 0.49, 0.35, 2.0},
+                               {64, 128, 1, 0.34, 0.26, 1.2},  {64, 64, 2, 0.37, 0.19, 1.2}};
+
+// The tile with the shortest estimated time, from tile `first` on: whole
+// rounds of workgroups, then a partial one whose stages lie between the two
+// measured times.
+int pick_tile(int64_t M, int64_t N, int64_t stages, int64_t n_cu, int first) {
+    int best = first;
+    double t_best = 0;
+    for (int i = first; i < static_cast<int>(sizeof(kTiles) / sizeof(kTiles[0])); ++i) {
+        const TileCost &c = kTiles[i];
+        const int64_t tiles = ((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
+        const int64_t slots = n_cu * c.per_cu, rem = tiles % slots;
+        const double f = static_cast<double>(rem) / slots;
+        double t = (tiles / slots) * (c.fixed + stages * c.full);
+        if (rem > 0) t += c.fixed + stages * (c.alone + (c.full - c.alone) * f);
+        if (i == first || t < t_best) {
+            best = i;
+            t_best = t;
+        }
+    }
+    return best;
+}
+
 template <typename T, bool QKV>
 hipError_t launch_typed(const void *x, const void *w, void *y, int M, int N, int K,
                         const QkvOut<T> &qo, hipStream_t stream) {
-    const int tiles_m = (M + kBM - 1) / kBM, tiles_n = (N + kBN - 1) / kBN;
-    const int64_t tiles = static_cast<int64_t>(tiles_m) * tiles_n;
-    if (tiles > 0x7fffffff) return hipErrorInvalidValue;
     int device = 0, n_cu = 0;
     hipError_t e = hipGetDevice(&device);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, device);
     if (e != hipSuccess) return e;
-    // Short reductions (K of at most kPersistK) run one persistent workgroup
-    // per CU, whose tiles stream without a pipeline refill; longer ones one
-    // workgroup per tile.
-    const int64_t blocks = K <= kPersistK && tiles > n_cu ? n_cu : tiles;
-    if (blocks < 1) return hipErrorInvalidValue;
-    linear_kernel<T, QKV><<<static_cast<unsigned>(blocks), kThreads, 0, stream>>>(
-        static_cast<const T *>(x), static_cast<const T *>(w), static_cast<T *>(y), M, N, K, tiles_m,
-        tiles_n, qo);
-    return hipGetLastError();
+    if (n_cu < 1) return hipErrorInvalidValue;
+    auto run = [&](auto tile) {
+        using C = decltype(tile);
+        return launch_tile<T, QKV, C>(static_cast<const T *>(x), static_cast<const T *>(w),
+                                      static_cast<T *>(y), M, N, K, qo, n_cu, stream);
+    };
+    // The rotation of fp32 features does not fit beside the 256 x 256 tile's
+    // accumulators and staged values.
+    constexpr bool kNoA = QKV && sizeof(T) == 4;
+    switch (pick_tile(M, N, static_cast<int64_t>(K) * sizeof(T) / 128, n_cu, kNoA ? 1 : 0)) {
+        case 0:
+            if constexpr (!kNoA) return run(TileA{});
+            else break;
+        case 1: return run(TileB{});
+        case 2: return run(TileC{});
+        case 3: return run(TileD{});
+        case 4: return run(TileE{});
+        case 5: return run(TileF{});
+    }
+    return hipErrorInvalidValue;
 }
 
 template <typename T>
@@ -471,7 +545,7 @@ QkvOut<T> qkv_out(void *q, void *k, void *v, const float *table, const RopeAxes 
 
 }  // namespace
 
-int linear_k_multiple() { return kBK; }
+int linear_k_multiple() { return 64; }
 
 hipError_t launch_linear(const void *x, const void *w, void *y, int M, int N, int K, int dtype,
                          hipStream_t stream) {

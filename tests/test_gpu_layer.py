@@ -203,3 +203,41 @@ def test_layer_forward_is_the_three_calls(hcms):
     torch.cuda.synchronize()
     ctx.close()
     assert torch.equal(bits(y.cpu()), bits(y2.cpu()))
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("M,N,K", [
+    (65, 72, 64), (130, 1032, 1024),                          # 64 x 64, one stage and many
+    (1025, 1928, 256), (1025, 15368, 64),                     # 128 x 128 and its remainders
+    (70, 15368, 512),                                         # 64 x 128, few rows
+    (3001, 3008, 64), (3065, 4104, 320), (2000, 4880, 192),   # 192 x 256, 256 x 192
+    (4001, 4008, 64), (4100, 8200, 192)])                     # 256 x 256, one round and more
+def test_linear_tiles_match_oracle(hcms, M, N, K, dtype):
+    """Every tile of the GEMM on 256 compute units, with ragged rows and
+    columns and reductions of one stage, odd and even counts.  One rounding of
+    the exact product: bounds as in test_linear_matches_oracle."""
+    log(f"[linear tiles] M={M} N={N} K={K} {dtype}")
+    g = torch.Generator().manual_seed(M + N + K)
+    x = torch.randn(M, K, generator=g).to(dtype)
+    w = (torch.randn(N, K, generator=g) / K ** 0.5).to(dtype)
+    got = hcms.linear(x.cuda(), w.cuda())
+    rows = np.unique(np.concatenate([np.arange(0, M, max(1, M // 97)), [M - 1]]))
+    want = olayer.linear(_f64(x[rows]), _f64(w).T)
+    _check_close(_f64(got[torch.from_numpy(rows).cuda()]), want, "linear",
+                 2.0 ** -8 if dtype == torch.bfloat16 else 2.0 ** -7)
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("S,D,H,d", [(97, 64, 3, 8), (1301, 192, 5, 128), (3001, 128, 8, 128),
+                                     (2600, 64, 13, 128), (4100, 128, 10, 128)])
+def test_qkv_tiles_match_linear(hcms, S, D, H, d, dtype):
+    """The split of the QKV epilogue on every tile, at head boundaries inside
+    and across segments: without a rotation q, k, v hold the bits of the plain
+    product's columns."""
+    log(f"[qkv tiles] S={S} D={D} H={H} d={d} {dtype}")
+    g = torch.Generator().manual_seed(S + D)
+    x = torch.randn(S, D, generator=g).to(dtype).cuda()
+    w = (torch.randn(3 * H * d, D, generator=g) / D ** 0.5).to(dtype).cuda()
+    qkv = torch.stack(hcms.qkv_projection(x, w, H, d), dim=1)
+    plain = hcms.linear(x, w).view(S, 3, H, d)
+    assert torch.equal(bits(qkv.cpu()), bits(plain.cpu()))
