@@ -14,7 +14,7 @@
  * Conventions for every entry point
  *   - Buffers are device memory owned by the caller, contiguous, row-major,
  *     16-byte aligned.  The library allocates no device memory on any call
- *     except hcms_ctx_create (which creates events only).
+ *     except hcms_ctx_create (events, and 70 MiB to share tiles in).
  *   - `stream` arguments are hipStream_t handles passed as void*.  NULL is the
  *     null stream of the current device.  Streams are borrowed, never destroyed.
  *   - All compute calls are asynchronous and stream-ordered; a kernel fault
@@ -321,13 +321,14 @@ HCMS_API int hcms_plan(int n_chunks, int mode, hcms_op *ops, int cap);
  * sum_c ceil(W_c / (n_cu * B)) rounds of workgroups; two lanes pool them,
  * ceil(sum_c W_c / (n_cu * B)).  A launch's last round leaves
  * n_cu * B * ceil(W_c / (n_cu * B)) - W_c slots idle.  Returns
- * HCMS_MODE_SERIAL for one chunk; HCMS_MODE_LANES when pooling saves a round;
- * otherwise, for d = 128 with bf16 storage, HCMS_MODE_FUSED when some launch
+ * HCMS_MODE_SERIAL for one chunk; HCMS_MODE_LANES when pooling saves rounds,
+ * rounds saved * S >= 4096 (shorter rounds cost less than the lanes'
+ * synchronisations); otherwise, for d = 128 with bf16 storage, HCMS_MODE_FUSED when some launch
  * leaves at least n_cu * B / 8 slots idle (where the neighbouring chunks'
  * copies ride) and HCMS_MODE_SERIAL when none does (the fused plan would run
  * the serial plan's launches); for the other kernels HCMS_MODE_INLINE when
  * chunk 0's launch leaves that many slots idle (where packs 1..C-1 run) and
- * HCMS_MODE_SERIAL otherwise.  Errors: HCMS_ERR_SHAPE (S < 0, d),
+ * S >= 4096, and HCMS_MODE_SERIAL otherwise.  Errors: HCMS_ERR_SHAPE (S < 0, d),
  * HCMS_ERR_DTYPE, HCMS_ERR_ARG (n_cu < 1), HCMS_ERR_NULL or HCMS_ERR_CHUNKS.
  * Host only.
  */
@@ -372,8 +373,9 @@ HCMS_API int hcms_model_fit(const int *chunk_counts, const double *times, int n,
  * which lasts t_round (g0 + (1 - g0) f) (the clock rises when part of the
  * chip idles; g0 = 1: a partial round costs a full one).  When the attention
  * kernel splits that round's tiles by key segments (hcms_forward's d = 128
- * bf16 launches: 3 rem <= n three ways, else 2 rem <= n two ways, with S of
- * 12 key blocks or more; in the lanes plan the last launch of each lane
+ * bf16 launches; the model counts 3 rem <= n three ways, else 2 rem <= n two
+ * ways, with S of 12 key blocks or more, and no further sharing; in the lanes
+ * plan the last launch of each lane
  * splits the rem = sum W mod n tiles past the pooled rounds) the round holds
  * ways rem workgroups and lasts a third (three ways) or two thirds (two ways)
  * as long.  Every launch on the critical path adds `drain` rounds (its last
@@ -537,7 +539,8 @@ HCMS_API int hcms_forward_slots(hcms_ctx *ctx, const void *q_seq, const void *k_
  * each chunk's backward launches (these carry none).  HCMS_MODE_AUTO runs lanes
  * when the context's score-gradient workspace applies and there are two chunks
  * or more (one chunk's HBM-bound dQ product then overlaps the next chunk's
- * key-parallel launch), else what hcms_auto_mode picks.  Every mode and
+ * key-parallel launch), else what hcms_auto_mode picks with 512 in place of
+ * 4096 (its rounds last longer).  Every mode and
  * chunking gives bit-identical gradients.  Errors: as hcms_forward and
  * hcms_attention_backward.
  */

@@ -335,7 +335,7 @@ int plan_size(int C, int mode) {
 }  // namespace
 
 // The plan HCMS_MODE_AUTO runs (hcms_auto_mode without validation).
-int hcms::auto_plan(int S, int d, int dtype, const int *sizes, int C, int n_cu) {
+int hcms::auto_plan(int S, int d, int dtype, const int *sizes, int C, int n_cu, int64_t lanes_keys) {
     if (C == 1) return HCMS_MODE_SERIAL;
     const int64_t br = hcms::attention_queries_per_block(d);
     const int64_t slots = static_cast<int64_t>(n_cu) * hcms::attention_blocks_per_cu(d);
@@ -355,20 +355,26 @@ int hcms::auto_plan(int S, int d, int dtype, const int *sizes, int C, int n_cu) 
         some_idle = some_idle || enough;
         if (c == 0) first_idle = enough;
     }
-    // Two lanes pool the chunks' partial rounds: a whole round saved.
-    if (rounds > (total + slots - 1) / slots) return HCMS_MODE_LANES;
+    // Two lanes pool the chunks' partial rounds: whole rounds saved, of about
+    // 0.02 us per key, for four synchronisations of 6 us and launches that
+    // start later.  Below lanes_keys the plans without any are faster: two
+    // chunks of S = 512 61 us in lanes, 36 serial; {4, 4} of S = 3001 88 in
+    // lanes, 78 fused (S = 32760 {5, 5}: lanes 4.3 ms, fused 4.7).
+    const int64_t saved = rounds - (total + slots - 1) / slots;
+    if (saved > 0 && saved * S >= lanes_keys) return HCMS_MODE_LANES;
     // The fused plan moves copies only on CUs a launch's last round leaves
     // idle; with none anywhere it would run the serial plan's launches.
     if (d == 128 && dtype == HCMS_BF16) return some_idle ? HCMS_MODE_FUSED : HCMS_MODE_SERIAL;
     // The inline plan pays four synchronisations to run packs 1..C-1 beside
-    // attention 0's last round: only worth it when that round has idle CUs.
-    return first_idle ? HCMS_MODE_INLINE : HCMS_MODE_SERIAL;
+    // attention 0's last round: only worth it when that round has idle CUs
+    // and lasts (S = 512: 85 us inline, 36 serial).
+    return first_idle && S >= lanes_keys ? HCMS_MODE_INLINE : HCMS_MODE_SERIAL;
 }
 
 namespace {
 
 int auto_mode(int S, int d, int dtype, const int *sizes, int C, int n_cu) {
-    return hcms::auto_plan(S, d, dtype, sizes, C, n_cu);
+    return hcms::auto_plan(S, d, dtype, sizes, C, n_cu, hcms::kForwardLanesKeys);
 }
 
 // Saves the current device, switches to `dev`, restores on scope exit.
@@ -461,7 +467,7 @@ namespace {
 int check_schedule(hcms_ctx *ctx, int P, int S, int H, int d, float scale, const int *chunk_sizes,
                    int n_chunks, int dtype, int *mode, int *log2u, void *main_stream,
                    void *copy_stream, void *compute_stream, bool slotted = false,
-                   bool prefer_lanes = false) {
+                   bool backward = false, bool prefer_lanes = false) {
     int st;
     const int m = *mode;
     if (!plan_mode(m) && m != HCMS_MODE_AUTO)
@@ -482,7 +488,9 @@ int check_schedule(hcms_ctx *ctx, int P, int S, int H, int d, float scale, const
     if ((m == HCMS_MODE_PIPELINED || m == HCMS_MODE_SLOTS) &&
         (copy_stream == compute_stream || copy_stream == main_stream || compute_stream == main_stream))
         return fail(HCMS_ERR_ARG, "pipelined and slots modes need three distinct streams");
-    int r = m == HCMS_MODE_AUTO ? auto_mode(S, d, dtype, chunk_sizes, n_chunks, ctx->n_cu) : m;
+    int r = m != HCMS_MODE_AUTO ? m
+            : hcms::auto_plan(S, d, dtype, chunk_sizes, n_chunks, ctx->n_cu,
+                              backward ? hcms::kBackwardLanesKeys : hcms::kForwardLanesKeys);
     // The backward with stored score gradients: one chunk's HBM-bound dQ
     // product overlaps the next chunk's key-parallel launch in lanes.
     if (m == HCMS_MODE_AUTO && prefer_lanes && n_chunks >= 2 && compute_stream != main_stream)
@@ -1189,11 +1197,11 @@ int hcms_ctx_create(int device, int max_chunks, hcms_ctx **out) {
         }
         ctx->events.push_back(ev);
     }
-    // Split scratch, two regions of n_cu slots and n_cu counters each.  If it
-    // cannot be had, launches keep every tile whole (same results).
+    // Split scratch, two regions of 2 n_cu slots and as many counters each.  If
+    // it cannot be had, launches split no tile by segments (same results).
     {
         const int64_t slot = hcms::attention_split_slot_bytes();
-        const int64_t n = ctx->n_cu;
+        const int64_t n = 2 * int64_t{ctx->n_cu};
         const int64_t region = n * slot + n * 4;
         void *mem = nullptr;
         if (hipMalloc(&mem, 2 * region) == hipSuccess && mem) {
@@ -1420,7 +1428,7 @@ int hcms_backward(hcms_ctx *ctx, const void *dout_seq, void *dq_seq, void *dk_se
     const int64_t ds_head = hcms::attention_backward_ds_head_bytes(S, d, dtype);
     const bool ds_path = ctx->ds != nullptr && ds_head > 0 && ctx->ds_region >= ds_head;
     if ((st = check_schedule(ctx, P, S, H, d, scale, chunk_sizes, n_chunks, dtype, &mode, &log2u,
-                             main_stream, copy_stream, compute_stream, false, ds_path)) != HCMS_OK)
+                             main_stream, copy_stream, compute_stream, false, true, ds_path)) != HCMS_OK)
         return st;
     for (int i = 0; i < 12; ++i)
         if (S > 0 && !aligned16(all[i])) return fail(HCMS_ERR_ALIGN, "buffers must be 16-byte aligned");

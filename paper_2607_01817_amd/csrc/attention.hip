@@ -718,21 +718,25 @@ __device__ inline void run_riders(const Riders &r, unsigned rider, unsigned n_ri
     }
 }
 
-// Tiles split over several workgroups (the launch's last, partial round of
-// tiles; see plan_split).  Workgroup n_whole + u computes segments of tile
-// n_whole + u % n_split: with 3 ways segment u / n_split, with 2 ways
-// segments 0-1 (u < n_split) or 2.  Each writes its partial state to slot
-// u (the normalised output in the stash layout, and (m, l, E) per query)
-// and counts itself in on its tile's counter; the last to arrive merges the
-// tile's partial states in segment order, writes the output and sets the
-// counter back to zero.
+// Tiles shared by several workgroups (the launch's last, partial round of
+// tiles; see plan_split).  Of the `units` = n_split * halves * ways workgroups
+// after the whole tiles', workgroup u takes part u % parts, parts = n_split *
+// halves: with halves = 2 the first or second 128 queries of tile n_whole +
+// part / 2, else the whole tile n_whole + part; and of it with ways = 3 key
+// segment u / parts, with ways = 1 all of them.  With 3 ways each writes its
+// partial state (the normalised output in the stash layout, and (m, l, E) per
+// query) to slot u and counts itself in on its part's counter; the last to
+// arrive merges the part's states in segment order, writes the output and
+// sets the counter back to zero.
 struct TailSplit {
-    char *part;      // n_split * ways slots of kStashB bytes
-    float4 *ml;      // n_split * ways slots of 256 (m, l, E, 0) per query
-    int *count;      // n_split counters, zero between launches
+    char *part;      // units slots of kStashB bytes (ways = 3)
+    float4 *ml;      // units slots of 256 (m, l, E, 0) per query
+    int *count;      // a counter per part, zero between launches
     int n_whole;     // tiles computed whole by one workgroup: the first n_whole
     int n_split;     // tiles split: the last n_split
-    int ways;        // 2 or 3
+    int halves;      // 1 or 2
+    int ways;        // 1 or 3
+    int units() const { return n_split * halves * ways; }
 };
 
 // The state of a query after some of its key segments: the maximum m of its
@@ -759,27 +763,32 @@ __device__ inline void quantise(f32x16 (&n)[4], int E) {
             n[dt][r] = __builtin_ldexpf(static_cast<float>(static_cast<_Float16>(__builtin_ldexpf(n[dt][r], -E))), E);
 }
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-// Chunk k (values 8k .. 8k + 7) of lane l at base + k * 1 KiB + 16 l.  The
-// pointers come from the stash or the split scratch; the compiler infers LDS
-// or global after inlining.
-__device__ inline void store_state(char *base, const f32x16 (&n)[4], int E, int lane) {
+// Chunk k (values 8k .. 8k + 7) of the state as stored.
+__device__ inline u32x4 state_chunk(const f32x16 (&n)[4], int E, int k) {
+    f16x8 h;
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        f16x8 h;
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-            h[i] = static_cast<_Float16>(__builtin_ldexpf(n[k >> 1][(k & 1) * 8 + i], -E));
-        *reinterpret_cast<f16x8 *>(base + k * 1024 + 16 * lane) = h;
-    }
+    for (int i = 0; i < 8; ++i) h[i] = static_cast<_Float16>(__builtin_ldexpf(n[k >> 1][(k & 1) * 8 + i], -E));
+    return __builtin_bit_cast(u32x4, h);
 }
-__device__ inline void load_state(f32x16 (&n)[4], const char *base, int E, int lane) {
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        const f16x8 h = *reinterpret_cast<const f16x8 *>(base + k * 1024 + 16 * lane);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) n[k >> 1][(k & 1) * 8 + i] = __builtin_ldexpf(static_cast<float>(h[i]), E);
+
+// Stored chunks by the memory they lie in: LDS (the stash), or the split
+// scratch, which workgroups of other XCDs write and read.  The scratch is
+// accessed past the XCDs' own L2 (write-through stores and loads that miss
+// it: agent scope), so that publishing a state needs no write-back of the
+// whole L2: with agent fences, which every wave of every workgroup issues,
+// 128 tiles of S = 4096 split two ways took about 125 us, 92 unsplit.
+struct LdsState {
+    const char *base;   // the lane's chunk 0
+    __device__ u32x4 chunk(int k) const { return *reinterpret_cast<const u32x4 *>(base + k * 1024); }
+};
+constexpr int kAgent = 16;   // cache policy: agent scope (sc1)
+struct ScratchState {
+    __amdgpu_buffer_rsrc_t r;
+    unsigned off;       // the lane's chunk 0
+    __device__ u32x4 chunk(int k) const {
+        return __builtin_amdgcn_raw_buffer_load_b128(r, off, k * 1024, kAgent);
     }
-}
+};
 
 // The state of one segment from its online softmax: N = O / l, in place.
 __device__ inline void segment_state(f32x16 (&o)[4], float l) {
@@ -803,14 +812,25 @@ __device__ inline void merge_weights(float mA, float lA, float mB, float lB, flo
     wa = a * inv;
     wb = b * inv;
 }
-// Merges a stored state (chunk k of lane l at base + k * 1 KiB + 16 l, scale
-// 2^E) into this lane's 64 values n, chunk by chunk: stored_is_a says whether
-// the stored state is A (the earlier segments) or B.
-__device__ inline void merge_stored(f32x16 (&n)[4], const char *base, int E, int lane, float wa,
-                                    float wb, bool stored_is_a) {
+// Reads a stored state of scale 2^E.
+template <typename Stored>
+__device__ inline void load_state(f32x16 (&n)[4], const Stored &st, int E) {
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
-        const f16x8 h = *reinterpret_cast<const f16x8 *>(base + k * 1024 + 16 * lane);
+        const f16x8 h = __builtin_bit_cast(f16x8, st.chunk(k));
+#pragma unroll
+        for (int i = 0; i < 8; ++i) n[k >> 1][(k & 1) * 8 + i] = __builtin_ldexpf(static_cast<float>(h[i]), E);
+    }
+}
+// Merges a stored state of scale 2^E into this lane's 64 values n, chunk by
+// chunk: stored_is_a says whether the stored state is A (the earlier segments)
+// or B.
+template <typename Stored>
+__device__ inline void merge_stored(f32x16 (&n)[4], const Stored &st, int E, float wa, float wb,
+                                    bool stored_is_a) {
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        const f16x8 h = __builtin_bit_cast(f16x8, st.chunk(k));
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             const float x = __builtin_ldexpf(static_cast<float>(h[i]), E);
@@ -826,7 +846,7 @@ __global__ __launch_bounds__(64 * dma::kWaves, dma::kWaves / 4) void attention_d
     __bf16 *__restrict__ o, float *__restrict__ lse, int S, int n_qtiles, float c, TailSplit tail,
     Riders riders) {
     using namespace dma;
-    const int n_attn = tail.n_whole + tail.n_split * tail.ways;
+    const int n_attn = tail.n_whole + tail.n_split * tail.halves * tail.ways;
     if constexpr (kRiders) {
         if (blockIdx.x >= static_cast<unsigned>(n_attn)) {
             run_riders(riders, blockIdx.x - n_attn, gridDim.x - n_attn);
@@ -844,25 +864,38 @@ __global__ __launch_bounds__(64 * dma::kWaves, dma::kWaves / 4) void attention_d
     // (head, query tile) pairs, so concurrent workgroups of an XCD stream the
     // same K/V blocks through its L2.
     const int b = blockIdx.x;
-    int logical, split_u = -1;
+    const int parts = tail.n_split * tail.halves;
+    int logical, half = -1, split_u = -1;
+    const int nkb = (S + kBC - 1) / kBC;
+    const int nseg = n_segments(nkb);
+    int g_first = 0, g_last = nseg;
     if (b < tail.n_whole) {
         const int nb = tail.n_whole;
         const int xcd = b & 7, per = nb >> 3, rem = nb & 7;
         logical = xcd * per + min(xcd, rem) + (b >> 3);
     } else {
-        split_u = b - tail.n_whole;
-        logical = tail.n_whole + split_u % tail.n_split;
+        const int u = b - tail.n_whole, part = u % parts;
+        logical = tail.n_whole + part / tail.halves;
+        if (tail.halves == 2) half = part & 1;
+        if (tail.ways > 1) {
+            split_u = u;
+            g_first = u / parts;
+            g_last = g_first + 1;
+        }
     }
-    const int head = logical / n_qtiles;
-    const int qtile = logical - head * n_qtiles;
-    const int nkb = (S + kBC - 1) / kBC;
-    const int nseg = n_segments(nkb);
-    int g_first = 0, g_last = nseg;
-    if (split_u >= 0) {
-        const int p = split_u / tail.n_split;
-        g_first = tail.ways == 3 ? p : 2 * p;
-        g_last = tail.ways == 3 ? p + 1 : (p == 0 ? 2 : 3);
+    // The tiles of 256 queries below S of every head first, then the heads'
+    // last, ragged tiles, which are the shorter ones.
+    const int n_heads = (tail.n_whole + tail.n_split) / n_qtiles, n_full = S / (kWaves * kQW);
+    int head, qtile;
+    if (logical < n_heads * n_full) {
+        head = logical / n_full;
+        qtile = logical - head * n_full;
+    } else {
+        head = logical - n_heads * n_full;
+        qtile = n_full;
     }
+    const int qbase = qtile * (kWaves * kQW) + (half > 0 ? kWaves / 2 * kQW : 0);
+    if (qbase >= S) return;   // the empty second half of a ragged tile
 
     const int64_t hoff = static_cast<int64_t>(head) * S * D;
     const int64_t hbytes = static_cast<int64_t>(S) * D * 2;
@@ -876,7 +909,10 @@ __global__ __launch_bounds__(64 * dma::kWaves, dma::kWaves / 4) void attention_d
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int li = lane & 31;
     const int g = lane >> 5;
-    const int q0 = (qtile * kWaves + wave) * kQW;
+    const int q0 = qbase + wave * kQW;
+    // A wave without queries (past S, or the other half's) only loads: then
+    // the wave it shares a SIMD with runs a step in about 0.56 of the time.
+    const bool computes = q0 < S && (half < 0 || wave < kWaves / 2);
 
     bf16x8 qreg[KK];
 #pragma unroll
@@ -942,6 +978,21 @@ __global__ __launch_bounds__(64 * dma::kWaves, dma::kWaves / 4) void attention_d
         for (int j = 0; j <= kDist; ++j) {
             issue_k(j);
             if (j < kDist) issue_v(j);
+        }
+        if (!computes) {   // its share of the loads, and every barrier
+            wait_vm<4 * kDist>();
+            __syncthreads();
+            wait_vm<4 * kDist - 4>();
+            __syncthreads();
+            for (int j = 0; j + 1 < nb; ++j) {
+                issue_k(j + 1 + kDist);
+                issue_v(j + kDist);
+                wait_vm<4 * (kDist - 1)>();
+                __syncthreads();
+            }
+            wait_vm<0>();
+            __syncthreads();
+            return;
         }
         wait_vm<4 * kDist>();  // K_0 landed
         __syncthreads();
@@ -1084,15 +1135,20 @@ __global__ __launch_bounds__(64 * dma::kWaves, dma::kWaves / 4) void attention_d
         __syncthreads();  // every wave is done with the buffers the next segment loads into
     };
 
-    const int qi = q0 + li;
-    char *const my_stash = stash + wave * kStashWaveB;
+    // The lane index anew, so that nothing below holds a register in the key
+    // loop (248 are all there are).
+    const auto lane_id = []() {
+        return static_cast<int>(__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0)));
+    };
     float m_s = 0.f, l_s = 0.f;       // merged state of the segments so far
     int e_s = 0;
     bool normalised = false;          // oacc holds N (several segments) or O (one)
     for (int gs = g_first; gs < g_last; ++gs) {
         const int b0 = seg_begin(nkb, gs);
         segment(b0, seg_begin(nkb, gs + 1) - b0);
+        if (!computes) continue;
         const float l_g = halves_sum(lsum);
+        char *const mine = stash + wave * kStashWaveB + 16 * lane_id();
         if (nseg == 1) {  // one segment: its state is the result
             m_s = m;
             l_s = l_g;
@@ -1111,54 +1167,79 @@ __global__ __launch_bounds__(64 * dma::kWaves, dma::kWaves / 4) void attention_d
             // ... merged into the stored state of the earlier segments.
             float wa, wb;
             merge_weights(m_s, l_s, m, l_g, c, m_s, l_s, wa, wb);
-            merge_stored(oacc, my_stash, e_s, lane, wa, wb, true);
+            merge_stored(oacc, LdsState{mine}, e_s, wa, wb, true);
             if (gs + 1 < nseg) {   // segments 0-1 merged: quantised as a stored state
                 e_s = state_exponent(oacc);
                 quantise(oacc, e_s);
             }
         }
-        if (gs + 1 < g_last) store_state(my_stash, oacc, e_s, lane);  // read back by this lane only
+        if (gs + 1 < g_last) {   // read back by this lane only
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                *reinterpret_cast<u32x4 *>(mine + k * 1024) =
+                    state_chunk(oacc, e_s, k);
+        }
     }
 
+    const int lane2 = lane_id(), li2 = lane2 & 31, g2 = lane2 >> 5, qi = q0 + li2;
     if (split_u >= 0) {
         // A share of a split tile: publish this workgroup's partial state, and
-        // the last of the tile's workgroups to arrive merges them all.
-        const int slot = split_u;
-        store_state(tail.part + static_cast<int64_t>(slot) * kStashB + wave * kStashWaveB, oacc, e_s, lane);
-        if (g == 0)
-            tail.ml[slot * 256 + wave * kQW + li] = make_float4(m_s, l_s, __builtin_bit_cast(float, e_s), 0.f);
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        // the last of the part's workgroups to arrive merges them all.  The
+        // stores are complete at agent scope (vmcnt) before the barrier in
+        // front of the count.
+        const auto scratch = [&](int slot) {
+            return ScratchState{head_rsrc(tail.part + static_cast<int64_t>(slot) * kStashB, kStashB),
+                                static_cast<unsigned>(wave * kStashWaveB + 16 * lane2)};
+        };
+        const auto stats = [&](int slot) {
+            return head_rsrc(tail.ml + static_cast<int64_t>(slot) * (kWaves * kQW), kWaves * kQW * sizeof(float4));
+        };
+        const unsigned stat_off = (wave * kQW + li2) * sizeof(float4);
+        if (computes) {
+            // Without a scalar offset: the data registers of a 16-byte buffer
+            // store with one were overwritten by the next instruction before
+            // the store had read them (no wait state is inserted there).
+            const ScratchState st = scratch(split_u);
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                __builtin_amdgcn_raw_buffer_store_b128(state_chunk(oacc, e_s, k), st.r, st.off + k * 1024, 0, kAgent);
+            if (g2 == 0) {
+                const f32x4 ml = {m_s, l_s, __builtin_bit_cast(float, e_s), 0.f};
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, ml), stats(split_u), stat_off, 0, kAgent);
+            }
+        }
+        wait_vm<0>();
         // The stash is free now: its first word carries thread 0's arrival
         // count to the other waves.
         volatile int *arrived = reinterpret_cast<volatile int *>(stash);
         __syncthreads();
-        const int tt = split_u % tail.n_split;
-        if (tid == 0) *arrived = atomicAdd(&tail.count[tt], 1);
+        const int part = split_u % parts;
+        if (wave == 0 && lane2 == 0) *arrived = atomicAdd(&tail.count[part], 1);
         __syncthreads();
         if (*arrived != tail.ways - 1) return;
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        // The tile's partial states in segment order (slots tt + p n_split),
-        // this workgroup's own read back like the others.
-        auto slot_of = [&](int p) { return tt + p * tail.n_split; };
-        auto part_of = [&](int p) {
-            return tail.part + static_cast<int64_t>(slot_of(p)) * kStashB + wave * kStashWaveB;
+        if (wave == 0 && lane2 == 0) atomicExch(&tail.count[part], 0);   // ready for the next launch on this scratch
+        if (!computes) return;
+        // The part's states in segment order (slots part + p parts), this
+        // workgroup's own read back like the others.
+        const auto stat = [&](int p) {
+            return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(stats(part + p * parts), stat_off, 0, kAgent));
         };
-        float4 st = tail.ml[slot_of(0) * 256 + wave * kQW + li];
-        m_s = st.x;
-        l_s = st.y;
-        load_state(oacc, part_of(0), __builtin_bit_cast(int, st.z), lane);
+        f32x4 st = stat(0);
+        m_s = st[0];
+        l_s = st[1];
+        load_state(oacc, scratch(part), __builtin_bit_cast(int, static_cast<float>(st[2])));
         for (int p = 1; p < tail.ways; ++p) {
-            st = tail.ml[slot_of(p) * 256 + wave * kQW + li];
+            st = stat(p);
             float wa, wb;
-            merge_weights(m_s, l_s, st.x, st.y, c, m_s, l_s, wa, wb);
-            merge_stored(oacc, part_of(p), __builtin_bit_cast(int, st.z), lane, wa, wb, false);
+            merge_weights(m_s, l_s, st[0], st[1], c, m_s, l_s, wa, wb);
+            merge_stored(oacc, scratch(part + p * parts), __builtin_bit_cast(int, static_cast<float>(st[2])), wa, wb, false);
             if (p + 1 < tail.ways) quantise(oacc, state_exponent(oacc));   // segments 0-1 merged
         }
-        if (tid == 0) atomicExch(&tail.count[tt], 0);   // ready for the next launch on this scratch
     }
+    if (!computes) return;
 
     const float inv = normalised ? 1.0f : 1.0f / l_s;
-    if (lse != nullptr && g == 0 && qi < S)
+    if (lse != nullptr && g2 == 0 && qi < S)
         lse[static_cast<int64_t>(head) * S + qi] = m_s * c + __builtin_amdgcn_logf(l_s);
     if (qi < S) {
         __bf16 *orow = oh + static_cast<int64_t>(qi) * D;
@@ -1168,7 +1249,7 @@ __global__ __launch_bounds__(64 * dma::kWaves, dma::kWaves / 4) void attention_d
             for (int rb = 0; rb < 4; ++rb) {
                 const f32x4 x = {oacc[dt][rb * 4 + 0] * inv, oacc[dt][rb * 4 + 1] * inv,
                                  oacc[dt][rb * 4 + 2] * inv, oacc[dt][rb * 4 + 3] * inv};
-                store4(orow + dt * 32 + rb * 8 + g * 4, x);
+                store4(orow + dt * 32 + rb * 8 + g2 * 4, x);
             }
     }
 }
@@ -1192,28 +1273,49 @@ struct Shape {
 };
 
 // The split of a d = 128 bf16 launch of W tiles on n_cu CUs (one workgroup
-// per CU): when its last round holds rem = W mod n_cu tiles and 3 rem (or
-// 2 rem) workgroups fit in one round, those tiles are split three (or two)
-// ways by key segments, so the last round lasts a third (two thirds) as
-// long.  With sp->tail >= 0 the last min(tail, W) tiles are the ones split:
-// a launch whose last round is shared with another stream's launch splits
-// the tiles that close the pooled rounds.  Needs scratch (none: every tile
-// whole, the same results).
-TailSplit plan_split(int64_t W, int S, const SplitScratch *sp) {
-    TailSplit t{nullptr, nullptr, nullptr, static_cast<int>(W), 0, 1};
+// per CU): the last round's t = W mod n_cu tiles are shared by more workgroups
+// where that shortens it.  In rounds, of which a whole tile takes 1:
+//   three key segments of halves of 128 queries   0.25, and 4 us to merge
+//   three key segments                            0.33, and 4 us
+//   halves (half the waves only load)             0.65, to 0.85 with every CU busy
+//   three key segments in two rounds              0.67, and 4 us
+// and the first that fits is taken, in this order: 64 tiles of S = 4096 take
+// 92 us whole, 64 in halves, 38 in thirds; 128 tiles 92, 79 and, in thirds
+// over two rounds, 88; 155 tiles of S = 7800 165 and 145.  Segments need
+// scratch (none: halves or whole tiles, the same
+// results).  With sp->tail >= 0, t is that and the last
+// min(tail, W) tiles are split: a launch whose last round is shared with
+// another stream's launch splits the tiles that close the pooled rounds.
+TailSplit plan_split(int64_t W, int S, int n_cu, const SplitScratch *sp) {
+    TailSplit p{nullptr, nullptr, nullptr, static_cast<int>(W), 0, 1, 1};
     const int nkb = (S + kBC - 1) / kBC;
-    if (!sp || !sp->part || sp->n_cu < 2 || dma::n_segments(nkb) != dma::kSeg) return t;
-    const int64_t n = sp->n_cu, rem = sp->tail >= 0 ? std::min(sp->tail, W) : W % n;
-    if (rem == 0) return t;
-    const int ways = 3 * rem <= n ? 3 : 2 * rem <= n ? 2 : 0;
-    if (ways == 0 || rem * ways > sp->slots || rem > sp->counters) return t;
-    t.part = static_cast<char *>(sp->part);
-    t.ml = static_cast<float4 *>(sp->ml);
-    t.count = sp->count;
-    t.n_whole = static_cast<int>(W - rem);
-    t.n_split = static_cast<int>(rem);
-    t.ways = ways;
-    return t;
+    const int64_t n = n_cu, t = sp && sp->tail >= 0 ? sp->tail : W % n, rem = std::min(t, W);
+    if (n < 2 || rem == 0) return p;
+    auto scratch = [&](int halves) {
+        return sp && sp->part && dma::n_segments(nkb) == dma::kSeg && rem * halves * dma::kSeg <= sp->slots &&
+               rem * halves <= sp->counters;
+    };
+    if (6 * t <= n && scratch(2)) p.halves = 2, p.ways = 3;
+    else if (3 * t <= n && scratch(1)) p.ways = 3;
+    else if (2 * t <= n) p.halves = 2;
+    else if (3 * t <= 2 * n && scratch(1)) p.ways = 3;
+    else return p;
+    if (p.ways > 1) {
+        p.part = static_cast<char *>(sp->part);
+        p.ml = static_cast<float4 *>(sp->ml);
+        p.count = sp->count;
+    }
+    p.n_whole = static_cast<int>(W - rem);
+    p.n_split = static_cast<int>(rem);
+    return p;
+}
+
+// Compute units of the current device.
+hipError_t current_cus(int *n_cu) {
+    int device = 0;
+    hipError_t e = hipGetDevice(&device);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(n_cu, hipDeviceAttributeMultiprocessorCount, device);
+    return e;
 }
 
 template <int D, typename T>
@@ -1225,8 +1327,11 @@ hipError_t launch_typed(const void *q, const void *k, const void *v, void *o, fl
     if (blocks > 0x7fffffff) return hipErrorInvalidValue;
     if constexpr (D == dma::kD && sizeof(T) == 2 && kLdsDma) {
         static_assert(Sh::NT == 1 && Sh::WAVES == dma::kWaves, "the DMA kernel covers 256 queries in 8 waves");
-        const TailSplit t = plan_split(blocks, S, split);
-        const int64_t grid = t.n_whole + static_cast<int64_t>(t.n_split) * t.ways;
+        int n_cu = split ? split->n_cu : 0;
+        if (!split)
+            if (const hipError_t e = current_cus(&n_cu); e != hipSuccess) return e;
+        const TailSplit t = plan_split(blocks, S, n_cu, split);
+        const int64_t grid = static_cast<int64_t>(t.n_whole) + t.units();
         if (grid > 0x7fffffff) return hipErrorInvalidValue;
         attention_dma_kernel<false><<<static_cast<unsigned>(grid), 64 * dma::kWaves, 0, stream>>>(
             static_cast<const __bf16 *>(q), static_cast<const __bf16 *>(k), static_cast<const __bf16 *>(v),
@@ -1246,15 +1351,11 @@ int attention_blocks_per_cu(int d) { return d == 128 ? Shape<128>::PER_CU : Shap
 
 int64_t attention_split_slot_bytes() { return dma::kStashB + 256 * int64_t{sizeof(float4)}; }
 
-int attention_split_ways(int64_t W, int S, int d, int dtype, int n_cu, int64_t tail) {
+int attention_split_ways(int64_t W, int S, int d, int dtype, int n_cu) {
     if (!(kLdsDma && d == dma::kD && dtype == 0)) return 1;
-    SplitScratch sp{};
-    sp.part = sp.ml = reinterpret_cast<void *>(uintptr_t{256});   // placeholders: never dereferenced
-    sp.n_cu = n_cu;
-    sp.slots = sp.counters = n_cu;
-    sp.tail = tail;
-    const TailSplit t = plan_split(W, S, &sp);
-    return t.n_split > 0 ? t.ways : 1;
+    const int64_t rem = W % n_cu;
+    if (rem == 0 || dma::n_segments((S + kBC - 1) / kBC) != dma::kSeg) return 1;
+    return 3 * rem <= n_cu ? 3 : 2 * rem <= n_cu ? 2 : 1;
 }
 
 hipError_t launch_attention(const void *q, const void *k, const void *v, void *o, float *lse, int S,
@@ -1283,8 +1384,8 @@ hipError_t launch_attention_riding(const void *q, const void *k, const void *v, 
         return launch_attention(q, k, v, o, lse, S, n_heads, d, scale_log2e, dtype, split, stream);
     using Sh = Shape<dma::kD>;
     const int64_t n_qtiles = (S + Sh::BR - 1) / Sh::BR;
-    const TailSplit t = plan_split(n_qtiles * n_heads, S, split);
-    const int64_t n_attn = t.n_whole + static_cast<int64_t>(t.n_split) * t.ways;
+    const TailSplit t = plan_split(n_qtiles * n_heads, S, n_cu, split);
+    const int64_t n_attn = static_cast<int64_t>(t.n_whole) + t.units();
     const int64_t idle = (n_cu - n_attn % n_cu) % n_cu;
     Riders r{};
     r.S = S;

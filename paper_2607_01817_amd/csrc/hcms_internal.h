@@ -43,8 +43,11 @@ inline constexpr unsigned kCopyBesideAttentionLds = 40 * 1024;
 int attention_queries_per_block(int d);
 
 // The plan HCMS_MODE_AUTO runs for these chunks (hcms_auto_mode's rule; the
-// arguments are not validated).
-int auto_plan(int S, int d, int dtype, const int *sizes, int C, int n_cu);
+// arguments are not validated).  lanes_keys: rounds saved * S from which on
+// the plans with synchronisations pay; a round of the backward lasts several
+// times as long as one of the forward.
+inline constexpr int64_t kForwardLanesKeys = 4096, kBackwardLanesKeys = 512;
+int auto_plan(int S, int d, int dtype, const int *sizes, int C, int n_cu, int64_t lanes_keys);
 int attention_blocks_per_cu(int d);
 
 // Scratch for splitting a launch's last round of tiles over several
@@ -64,10 +67,11 @@ struct SplitScratch {
     int64_t tail = -1;
 };
 int64_t attention_split_slot_bytes();
-// Workgroups per split tile (2 or 3) a d = 128 bf16 launch of W tiles splits
-// its last `tail` tiles into on n_cu CUs (tail -1: W mod n_cu), or 1 when it
-// splits none.
-int attention_split_ways(int64_t W, int S, int d, int dtype, int n_cu, int64_t tail = -1);
+// Workgroups per split tile of the time model and of the mode rule, for a
+// launch of W tiles on n_cu CUs: 3 or 2 where the last round's W mod n_cu
+// tiles, shared by so many workgroups each, fit in one round, else 1.  (The
+// launch itself may share them further: halves of a tile, two rounds.)
+int attention_split_ways(int64_t W, int S, int d, int dtype, int n_cu);
 
 // lse, if not NULL, receives [n_heads][S] fp32 log2 softmax denominators:
 // P_ij = exp2(scale_log2e * <q_i, k_j> - lse_i).  split: NULL, or scratch

@@ -405,3 +405,34 @@ def test_timing_api_reports_every_chunk(hcms):
             ms = ctx.kernel_ms(kind)
             assert len(ms) == 6 and all(0 < x < 1000 for x in ms), (mode, kind, ms)
     ctx.close()
+
+
+@pytest.mark.parametrize("S,H,sizes", [
+    (4096, 5, (5,)),        # 80 tiles: three segments each
+    (4000, 2, (2,)),        # 32 tiles: segments of halves, a ragged last tile
+    (705, 1, (1,)),         # 3 tiles of the shortest split keys, an empty half
+    (3001, 10, (10,)),      # 120 tiles: halves
+    (7800, 5, (5,)),        # 155 tiles: segments over two rounds
+    (2100, 33, (33,)),      # 297 tiles: whole, then the ragged ones in segments
+    (1560, 40, (14, 13, 13)), (640, 30, (30,)), (200, 7, (4, 3))])
+def test_split_tails_bitwise_equal_head_by_head(hcms, S, H, sizes):
+    """Every way of sharing a launch's last round gives the bits of the other
+    ways: the forward in every plan and the plain attention, whole launches
+    against one head at a time, repeated on the same scratch."""
+    log(f"[tails] S={S} H={H} chunks={sizes}")
+    g = torch.Generator().manual_seed(S + H)
+    q, k, v = ((torch.randn(S, H, 128, generator=g) * 1.5).to(torch.bfloat16).cuda() for _ in range(3))
+    hm = [x.permute(1, 0, 2).contiguous() for x in (q, k, v)]
+    scale = 128 ** -0.5
+    want = torch.cat([hcms.attention(*(x[h:h + 1].contiguous() for x in hm), scale) for h in range(H)])
+    assert torch.equal(bits(hcms.attention(*hm, scale)), bits(want))
+    ref = torch.softmax((hm[0][0].float() @ hm[1][0].float().T) * scale, dim=1) @ hm[2][0].float()
+    assert float((want[0].float() - ref).abs().max()) <= 2e-2 * float(ref.abs().max())
+    want = want.permute(1, 0, 2).contiguous()
+    ctx = hcms.Context(max_chunks=8)
+    for mode in (hcms.MODE_SERIAL, hcms.MODE_LANES, hcms.MODE_FUSED, hcms.MODE_AUTO):
+        for rep in range(3):
+            out = ctx.forward(q, k, v, 1, scale, sizes, mode=mode)
+            assert torch.equal(bits(out), bits(want)), (mode, rep)
+    torch.cuda.synchronize()
+    ctx.close()
