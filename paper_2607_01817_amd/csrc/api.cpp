@@ -1057,7 +1057,7 @@ static int run_backward(const void *q, const void *k, const void *v, const void 
         auto atw = [off](void *p) { return static_cast<char *>(p) + off; };
         const hipError_t e = hcms::launch_attention_backward(
             at(q), at(k), at(v), at(out), at(dout), lse + soff, atw(dq), atw(dk), atw(dv),
-            delta + soff, ds, ds_bytes, S, chunk_sizes[i], d, scale, dtype, stream);
+            delta + soff, ds, ds_bytes, S, chunk_sizes[i], d, scale, dtype, 1, stream);
         if (e != hipSuccess) return hip_fail(e, "attention backward launch");
         h0 += chunk_sizes[i];
     }
@@ -1473,7 +1473,8 @@ int hcms_backward(hcms_ctx *ctx, const void *dout_seq, void *dq_seq, void *dk_se
                                                    at(o_hm, h0), at(do_hm, h0), lse + so,
                                                    at(dq_hm, h0), at(dk_hm, h0), at(dv_hm, h0),
                                                    delta + so, ds, ctx->ds_region, S, hc, d,
-                                                   scale, dtype, s);
+                                                   scale, dtype,
+                                                   mode == HCMS_MODE_LANES && n_chunks > 1 ? 2 : 1, s);
         }
         const void *src[3] = {at(dq_hm, h0), at(dk_hm, h0), at(dv_hm, h0)};
         void *dst[3] = {dq_seq, dk_seq, dv_seq};

@@ -286,7 +286,7 @@ __device__ inline void split3(float x, __bf16 &hi, __bf16 &mid, __bf16 &lo) {
 __global__ __launch_bounds__(64 * bdma::kWaves, bdma::kWaves / 4) void attention_dq_dma_kernel(
     const __bf16 *__restrict__ q, const __bf16 *__restrict__ k, const __bf16 *__restrict__ v,
     const __bf16 *__restrict__ o, const __bf16 *__restrict__ dout, const float *__restrict__ lse,
-    __bf16 *__restrict__ dq, float *__restrict__ delta, int S, int n_qtiles, float c, float scale) {
+    __bf16 *__restrict__ dq, float *__restrict__ delta, int S, int n_qtiles, int tile_rows, float c, float scale) {
     using namespace bdma;
     constexpr int D = kD, KK = D / 16, DT = D / 32;
     __shared__ __attribute__((aligned(1024))) char lds[2 * kNB * kTileB];
@@ -307,7 +307,8 @@ __global__ __launch_bounds__(64 * bdma::kWaves, bdma::kWaves / 4) void attention
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int li = lane & 31, g = lane >> 5;
-    const int qi = qtile * (kQW * kWaves) + wave * kQW + li;
+    const int qi = qtile * tile_rows + wave * kQW + li;
+    const bool computes = wave * kQW < tile_rows;
 
     bf16x8 qreg[KK], doreg[KK];
     float dpart = 0.f;
@@ -326,7 +327,7 @@ __global__ __launch_bounds__(64 * bdma::kWaves, bdma::kWaves / 4) void attention
     }
     const float Di = swap_halves_sum(dpart);
     const float Li = qi < S ? lse[static_cast<int64_t>(head) * S + qi] : 0.f;
-    if (g == 0 && qi < S) delta[static_cast<int64_t>(head) * S + qi] = Di;
+    if (computes && g == 0 && qi < S) delta[static_cast<int64_t>(head) * S + qi] = Di;
     drain_vm_loads();
 
     // Lane offsets: DMA sources (row r = 4 (2 wave + i) + lane / 16, chunk at
@@ -378,6 +379,15 @@ __global__ __launch_bounds__(64 * bdma::kWaves, bdma::kWaves / 4) void attention
     for (int blk = 0; blk < kDist; ++blk) issue(blk);
     wait_vm<4 * (kDist - 1)>();  // block 0 landed
     __syncthreads();
+    if (!computes) {   // half a tile: its share of the loads, and every barrier
+        for (int j = 0; j < nkb; ++j) {
+            issue(j + kDist);
+            wait_vm<4 * (kDist - 1)>();
+            __syncthreads();
+        }
+        wait_vm<0>();
+        return;
+    }
 
     typedef __attribute__((address_space(3))) bf16x4 LdsV4;
     // Block j in buffer P (P = j % kNB, or -1 when known only at run time);
@@ -550,7 +560,7 @@ __global__ __launch_bounds__(64 * bdma::kWaves, bdma::kWaves / 4) void attention
     const __bf16 *__restrict__ q, const __bf16 *__restrict__ k, const __bf16 *__restrict__ v,
     const __bf16 *__restrict__ dout, const float *__restrict__ lse, const float *__restrict__ delta,
     __bf16 *__restrict__ dk, __bf16 *__restrict__ dv, char *__restrict__ dsg, int S, int n_ktiles,
-    float c, float scale) {
+    int tile_rows, float c, float scale) {
     using namespace bdma;
     constexpr int D = kD, KK = D / 16, DT = D / 32, NT = 64 * kWaves, KEYS = kQW * kWaves;
     constexpr int QTB = kQB * kRowB;  // one block of 32 queries: 8 KiB
@@ -578,7 +588,8 @@ __global__ __launch_bounds__(64 * bdma::kWaves, bdma::kWaves / 4) void attention
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int li = lane & 31, g = lane >> 5;
-    const int key0 = ktile * KEYS;
+    const int key0 = ktile * tile_rows;
+    const bool computes = wave * kQW < tile_rows;
     const int kj = key0 + wave * kQW + li;
 
     bf16x8 kreg[KK];
@@ -589,6 +600,7 @@ __global__ __launch_bounds__(64 * bdma::kWaves, bdma::kWaves / 4) void attention
     constexpr int CH = D / 8;
 #pragma unroll
     for (int i = 0; i < KEYS * CH / NT; ++i) {
+        if (i * NT >= tile_rows * CH) break;
         const int u = tid + i * NT, row = u / CH, ch = u % CH;
         *reinterpret_cast<u32x4 *>(vrows + row * QLds<D>::RS + ch * 8) =
             load8<__bf16>(vr, static_cast<unsigned>((key0 + row) * D + ch * 8) * 2);
@@ -648,6 +660,15 @@ __global__ __launch_bounds__(64 * bdma::kWaves, bdma::kWaves / 4) void attention
     for (int blk = 0; blk < kDist; ++blk) issue(blk);
     wait_one_block();  // blocks 0 and 1 landed (and the V rows were stored)
     __syncthreads();
+    if (!computes) {   // half a tile: its share of the loads, and every barrier
+        for (int i = 0; i < nqb; ++i) {
+            issue(i + kDist);
+            wait_one_block();
+            __syncthreads();
+        }
+        wait_vm<0>();
+        return;
+    }
 
     // The statistics of a block's queries enter S and dP through one more
     // MFMA each: A holds -L_i / c (or -D_i) of query i = li in three bf16
@@ -668,14 +689,13 @@ __global__ __launch_bounds__(64 * bdma::kWaves, bdma::kWaves / 4) void attention
         return bf16x8{h, m, l, static_cast<__bf16>(-0x1p100f), 0, 0, 0, 0};
     };
     // Score gradients kept for the dQ product (kDs): the wave's 32 keys are
-    // key tile kw = 8 ktile + wave; the 32 x 32 tile of query block i sits at
+    // key tile kw = key0 / 32 + wave; the 32 x 32 tile of query block i sits at
     // byte ((head nqt + i / 8) nkw + kw) 16 KiB + (i % 8) 2 KiB of dsg
-    // (nqt = n_ktiles tiles of 256 queries), lane (li, g)'s dsb[h] at
+    // (nqt = ceil(S / 256) tiles of 256 queries, nkw = 8 nqt), lane (li, g)'s dsb[h] at
     // h KiB + 32 li + 16 g in it (see attention_dq_ds_kernel).
-    const int nkw = 8 * n_ktiles;
+    const int nqt = (S + KEYS - 1) / KEYS, nkw = 8 * nqt;
     char *const ds_wave =
-        kDs ? dsg + (static_cast<int64_t>(head) * n_ktiles * nkw + ktile * 8 + wave) * kDsGroupB
-            : nullptr;
+        kDs ? dsg + (static_cast<int64_t>(head) * nqt * nkw + key0 / kQW + wave) * kDsGroupB : nullptr;
     const int64_t ds_step = static_cast<int64_t>(nkw) * kDsGroupB;   // per 8 query blocks
     const unsigned ds_lane = li * 32 + g * 16;
 
@@ -788,9 +808,12 @@ __global__ __launch_bounds__(64 * bdma::kWaves, bdma::kWaves / 4) void attention
     else run(Flag<true>{});
     wait_vm<0>();
 
-    if (kj < S) {
-        __bf16 *krow = dk + hoff + static_cast<int64_t>(kj) * D;
-        __bf16 *vrow = dv + hoff + static_cast<int64_t>(kj) * D;
+    // The lane index anew, so that the key loop holds no register for it.
+    const int lane2 = static_cast<int>(__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0)));
+    const int g2 = lane2 >> 5, key = key0 + wave * kQW + (lane2 & 31);
+    if (key < S) {
+        __bf16 *krow = dk + hoff + static_cast<int64_t>(key) * D;
+        __bf16 *vrow = dv + hoff + static_cast<int64_t>(key) * D;
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
@@ -799,8 +822,8 @@ __global__ __launch_bounds__(64 * bdma::kWaves, bdma::kWaves / 4) void attention
                                   dkacc[dt][rb * 4 + 2] * scale, dkacc[dt][rb * 4 + 3] * scale};
                 const f32x4 xv = {dvacc[dt][rb * 4 + 0], dvacc[dt][rb * 4 + 1], dvacc[dt][rb * 4 + 2],
                                   dvacc[dt][rb * 4 + 3]};
-                store4(krow + dt * 32 + rb * 8 + g * 4, xk);
-                store4(vrow + dt * 32 + rb * 8 + g * 4, xv);
+                store4(krow + dt * 32 + rb * 8 + g2 * 4, xk);
+                store4(vrow + dt * 32 + rb * 8 + g2 * 4, xv);
             }
     }
 }
@@ -1149,13 +1172,29 @@ int64_t ds_head_bytes(int S) {
     return n * 8 * n * bdma::kDsGroupB;
 }
 
+// Rows per workgroup of the d = 128 bf16 kernels: 256, or 128 where twice the
+// workgroups still fit in one round on the CUs.  Then the waves without rows
+// only load, and those that compute have a SIMD each: 48 tiles of S = 3001
+// took 103 us (dQ) and 131 us (dK, dV) whole, 224 together, and take 160 in
+// halves.  lanes: launches of this size that run side by side (128 tiles in
+// each of two lanes: 427 us whole, 493 in halves).
+hipError_t tile_rows(int S, int n_heads, int lanes, int *rows, int *n_tiles) {
+    int device = 0, n_cu = 0;
+    hipError_t e = hipGetDevice(&device);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, device);
+    const int64_t tiles = (static_cast<int64_t>(S) + 255) / 256;
+    *rows = 2 * tiles * n_heads * lanes <= n_cu ? 128 : 256;
+    *n_tiles = static_cast<int>(tiles * (256 / *rows));
+    return e;
+}
+
 // The path with stored score gradients, for `group` heads at a time: D for
 // every head, then per group the key-parallel launch (dK, dV, and dS into
 // ds) and the dQ product over ds.
 hipError_t launch_bwd_ds(const __bf16 *q, const __bf16 *k, const __bf16 *v, const __bf16 *o,
                          const __bf16 *dout, const float *lse, __bf16 *dq, __bf16 *dk, __bf16 *dv,
-                         float *delta, char *ds, int S, int n_heads, int group, float c, float scale,
-                         hipStream_t stream) {
+                         float *delta, char *ds, int S, int n_heads, int group, int lanes, float c,
+                         float scale, hipStream_t stream) {
     constexpr int D = bdma::kD;
     const int nqb = (S + kQB - 1) / kQB;
     const int64_t n_waves = static_cast<int64_t>(nqb) * n_heads;
@@ -1169,10 +1208,12 @@ hipError_t launch_bwd_ds(const __bf16 *q, const __bf16 *k, const __bf16 *v, cons
     for (int h0 = 0; h0 < n_heads; h0 += group) {
         const int hg = min(group, n_heads - h0);
         const int64_t off = static_cast<int64_t>(h0) * S * D, soff = static_cast<int64_t>(h0) * S;
-        attention_dkdv_dma_kernel<true><<<static_cast<unsigned>(static_cast<int64_t>(n_tiles) * hg),
+        int rows = 0, n_rt = 0;
+        if ((e = tile_rows(S, hg, lanes, &rows, &n_rt)) != hipSuccess) return e;
+        attention_dkdv_dma_kernel<true><<<static_cast<unsigned>(static_cast<int64_t>(n_rt) * hg),
                                           KTile<D>::threads, 0, stream>>>(
             q + off, k + off, v + off, dout + off, lse + soff, delta + soff, dk + off, dv + off, ds, S,
-            n_tiles, c, scale);
+            n_rt, rows, c, scale);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         attention_dq_ds_kernel<<<static_cast<unsigned>(static_cast<int64_t>(n_qt) * hg),
                                  64 * dsq::kWaves, 0, stream>>>(k + off, ds, dq + off, S, n_qt,
@@ -1185,8 +1226,8 @@ hipError_t launch_bwd_ds(const __bf16 *q, const __bf16 *k, const __bf16 *v, cons
 template <int D, typename T>
 hipError_t launch_bwd_typed(const void *q, const void *k, const void *v, const void *o,
                             const void *dout, const float *lse, void *dq, void *dk, void *dv,
-                            float *delta, void *ds, int64_t ds_bytes, int S, int n_heads, float c,
-                            float scale, hipStream_t stream) {
+                            float *delta, void *ds, int64_t ds_bytes, int S, int n_heads, int lanes,
+                            float c, float scale, hipStream_t stream) {
     const int n_qt = (S + kQW * QTile<D>::waves - 1) / (kQW * QTile<D>::waves);
     const int64_t qblocks = static_cast<int64_t>(n_qt) * n_heads;
     const int n_tiles = (S + KTile<D>::keys - 1) / KTile<D>::keys;
@@ -1199,15 +1240,19 @@ hipError_t launch_bwd_typed(const void *q, const void *k, const void *v, const v
                                  static_cast<const __bf16 *>(v), static_cast<const __bf16 *>(o),
                                  static_cast<const __bf16 *>(dout), lse, static_cast<__bf16 *>(dq),
                                  static_cast<__bf16 *>(dk), static_cast<__bf16 *>(dv), delta,
-                                 static_cast<char *>(ds), S, n_heads, static_cast<int>(group), c,
+                                 static_cast<char *>(ds), S, n_heads, static_cast<int>(group), lanes, c,
                                  scale, stream);
     }
+    int rows = 256, n_rt = n_tiles;
+    if constexpr (D == bdma::kD && sizeof(T) == 2)
+        if (const hipError_t e = tile_rows(S, n_heads, lanes, &rows, &n_rt); e != hipSuccess) return e;
+    const unsigned rblocks = static_cast<unsigned>(static_cast<int64_t>(n_rt) * n_heads);
     if constexpr (D == bdma::kD && sizeof(T) == 2 && kDqDma) {
         static_assert(QTile<D>::waves == bdma::kWaves, "the DMA kernel covers 256 queries in 8 waves");
-        attention_dq_dma_kernel<<<static_cast<unsigned>(qblocks), QTile<D>::threads, 0, stream>>>(
+        attention_dq_dma_kernel<<<rblocks, QTile<D>::threads, 0, stream>>>(
             static_cast<const __bf16 *>(q), static_cast<const __bf16 *>(k), static_cast<const __bf16 *>(v),
             static_cast<const __bf16 *>(o), static_cast<const __bf16 *>(dout), lse,
-            static_cast<__bf16 *>(dq), delta, S, n_qt, c, scale);
+            static_cast<__bf16 *>(dq), delta, S, n_rt, rows, c, scale);
     } else {
         attention_dq_kernel<D, T><<<static_cast<unsigned>(qblocks), QTile<D>::threads, 0, stream>>>(
             static_cast<const T *>(q), static_cast<const T *>(k), static_cast<const T *>(v),
@@ -1218,10 +1263,10 @@ hipError_t launch_bwd_typed(const void *q, const void *k, const void *v, const v
     if (e != hipSuccess) return e;
     if constexpr (D == bdma::kD && sizeof(T) == 2 && kDkdvDma) {
         static_assert(KTile<D>::waves == bdma::kWaves, "the DMA kernel covers 256 keys in 8 waves");
-        attention_dkdv_dma_kernel<false><<<static_cast<unsigned>(blocks), KTile<D>::threads, 0, stream>>>(
+        attention_dkdv_dma_kernel<false><<<rblocks, KTile<D>::threads, 0, stream>>>(
             static_cast<const __bf16 *>(q), static_cast<const __bf16 *>(k), static_cast<const __bf16 *>(v),
             static_cast<const __bf16 *>(dout), lse, delta, static_cast<__bf16 *>(dk),
-            static_cast<__bf16 *>(dv), nullptr, S, n_tiles, c, scale);
+            static_cast<__bf16 *>(dv), nullptr, S, n_rt, rows, c, scale);
     } else {
         attention_dkdv_kernel<D, T><<<static_cast<unsigned>(blocks), KTile<D>::threads, 0, stream>>>(
             static_cast<const T *>(q), static_cast<const T *>(k), static_cast<const T *>(v),
@@ -1241,22 +1286,22 @@ int64_t attention_backward_ds_head_bytes(int S, int d, int dtype) {
 hipError_t launch_attention_backward(const void *q, const void *k, const void *v, const void *o,
                                      const void *dout, const float *lse, void *dq, void *dk,
                                      void *dv, float *delta, void *ds, int64_t ds_bytes, int S,
-                                     int n_heads, int d, float scale, int dtype,
+                                     int n_heads, int d, float scale, int dtype, int lanes,
                                      hipStream_t stream) {
     if (S == 0 || n_heads == 0) return hipSuccess;
     const float c = static_cast<float>(static_cast<double>(scale) * 1.4426950408889634);
     if (d == 128 && dtype == 0)
         return launch_bwd_typed<128, __bf16>(q, k, v, o, dout, lse, dq, dk, dv, delta, ds, ds_bytes, S,
-                                             n_heads, c, scale, stream);
+                                             n_heads, lanes, c, scale, stream);
     if (d == 64 && dtype == 0)
         return launch_bwd_typed<64, __bf16>(q, k, v, o, dout, lse, dq, dk, dv, delta, ds, ds_bytes, S,
-                                            n_heads, c, scale, stream);
+                                            n_heads, lanes, c, scale, stream);
     if (d == 128 && dtype == 1)
         return launch_bwd_typed<128, float>(q, k, v, o, dout, lse, dq, dk, dv, delta, ds, ds_bytes, S,
-                                            n_heads, c, scale, stream);
+                                            n_heads, lanes, c, scale, stream);
     if (d == 64 && dtype == 1)
         return launch_bwd_typed<64, float>(q, k, v, o, dout, lse, dq, dk, dv, delta, ds, ds_bytes, S,
-                                           n_heads, c, scale, stream);
+                                           n_heads, lanes, c, scale, stream);
     return hipErrorInvalidValue;
 }
 

@@ -108,11 +108,12 @@ hipError_t launch_attention_riding(const void *q, const void *k, const void *v, 
 // delta = <dO, O> and dq, then one key-parallel launch writing dk and dv.
 // With one (d = 128, bf16): delta first, then per group of
 // ds_bytes / head-bytes heads the key-parallel launch (dk, dv, and dS into
-// ds) and the dQ product over the stored dS.
+// ds) and the dQ product over the stored dS.  lanes: launches of this size
+// that may run side by side (1 or 2; a hint).
 hipError_t launch_attention_backward(const void *q, const void *k, const void *v, const void *o,
                                      const void *dout, const float *lse, void *dq, void *dk,
                                      void *dv, float *delta, void *ds, int64_t ds_bytes, int S,
-                                     int n_heads, int d, float scale, int dtype,
+                                     int n_heads, int d, float scale, int dtype, int lanes,
                                      hipStream_t stream);
 // Bytes of score-gradient workspace one head needs (0: the path does not
 // apply to this d and dtype).

@@ -254,3 +254,25 @@ def test_backward_pipeline_respects_events_under_delay(hcms, late, mode):
     for a, b, nm in zip(seen, ref, ("dq", "dk", "dv")):
         assert torch.equal(bits(a), bits(b)), (late, mode, nm)
     ctx.close()
+
+
+@pytest.mark.parametrize("S,H,ds", [(1100, 60, False), (513, 50, True), (300, 70, False)])
+def test_backward_halves_bitwise_equal_whole_tiles(hcms, S, H, ds):
+    """Tiles of 256 rows (many heads in a launch) and halves of 128 (one head
+    at a time) give the same gradients, with and without stored score
+    gradients, at row counts whose last half is empty, ragged and full."""
+    log(f"[backward halves] S={S} H={H} ds={ds}")
+    g = torch.Generator().manual_seed(S + H)
+    q, k, v, do = (torch.randn(H, S, 128, generator=g).to(torch.bfloat16).cuda() for _ in range(4))
+    scale = 128 ** -0.5
+    out, lse = hcms.attention_lse(q, k, v, scale)
+
+    def grads(h0, h1):
+        t = [x[h0:h1].contiguous() for x in (q, k, v, out, do, lse)]
+        ws = torch.empty((h1 - h0) * hcms.backward_ds_bytes(S, 128), dtype=torch.uint8, device="cuda") if ds else None
+        return hcms.attention_backward(*t, scale, ds=ws)
+
+    whole = grads(0, H)
+    for h in (0, 1, H - 1):
+        for a, b in zip(whole, grads(h, h + 1)):
+            assert torch.equal(bits(a[h]), bits(b[0])), h
