@@ -471,7 +471,9 @@ HCMS_API int hcms_ctx_kernel_ms(hcms_ctx *ctx, int kind, float *ms_out, int cap)
  *   workspaces, run attention on them into o_hm, and unpack o_hm's chunk into
  *   the head slots [h0_c, h0_c + H_c) of o_seq,
  * scheduled as hcms_plan(n_chunks, mode) describes (HCMS_MODE_AUTO: the mode
- * hcms_auto_mode picks for the device's CU count).  Returns when everything
+ * hcms_auto_mode picks for the device's CU count; with full workspaces and
+ * ceil(S / Br) H workgroups of at most one round, n_cu B, it runs the chunks
+ * joined into one, unless launches are timed).  Returns when everything
  * is enqueued; `main_stream` is ordered after all of it on return (no host
  * synchronisation).  All modes and all chunkings give bit-identical o_seq.
  *   q_seq, k_seq, v_seq, o_seq : device, [P][S/P][H][d]
@@ -540,7 +542,8 @@ HCMS_API int hcms_forward_slots(hcms_ctx *ctx, const void *q_seq, const void *k_
  * when the context's score-gradient workspace applies and there are two chunks
  * or more (one chunk's HBM-bound dQ product then overlaps the next chunk's
  * key-parallel launch), else what hcms_auto_mode picks with 512 in place of
- * 4096 (its rounds last longer).  Every mode and
+ * 4096 (its rounds last longer); it joins the chunks as hcms_forward does, with
+ * that workspace only if a region holds every head.  Every mode and
  * chunking gives bit-identical gradients.  Errors: as hcms_forward and
  * hcms_attention_backward.
  */

@@ -512,6 +512,20 @@ int check_schedule(hcms_ctx *ctx, int P, int S, int H, int d, float scale, const
     return HCMS_OK;
 }
 
+// Whether an automatic call runs its chunks joined into one: when all their
+// attention workgroups together fill no more than one round of the CUs, a
+// launch per chunk leaves most of them idle and costs more than any overlap
+// brings (S = 4096, 8 heads in {4, 4}: 104 us as two chunks, 88 joined; S =
+// 512, 4 heads in {2, 2}: 36 and 21).  The results are the same bits: they do
+// not depend on the chunking.  Not while the context times its launches,
+// which it reports chunk by chunk.
+bool joins_chunks(const hcms_ctx *ctx, int S, int H, int d) {
+    const int64_t br = hcms::attention_queries_per_block(d);
+    const int64_t slots = static_cast<int64_t>(ctx->n_cu) * hcms::attention_blocks_per_cu(d);
+    const bool timed = static_cast<int>(ctx->timed_chunks.size()) < ctx->timing_calls;
+    return !timed && (S + br - 1) / br * H <= slots;
+}
+
 // A copy op of the fused plan waiting for the attention launch it rides in.
 struct RiderOp {
     int kind, chunk, h0, hc;
@@ -680,7 +694,12 @@ auto copy_lds_reserve(int mode, int C) {
 }
 
 // Issues a validated hcms_forward (S > 0) in the resolved mode.
-int issue_forward(const ForwardArgs &f, int mode, int log2u) {
+int issue_forward(const ForwardArgs &args, int mode, int log2u) {
+    ForwardArgs f = args;
+    if (f.mode == HCMS_MODE_AUTO && f.slot_heads == 0 && joins_chunks(f.ctx, f.S, f.H, f.d)) {
+        f.chunk_sizes = &f.H;   // every plan of one chunk is the serial plan
+        f.n_chunks = 1;
+    }
     const int64_t head_bytes = static_cast<int64_t>(f.S) * f.d * elem_bytes(f.dtype);
     const float c_log2e = scale_log2e(f.scale);
     // Chunk c's head-major buffers: its heads of the full workspaces, or slot
@@ -1425,6 +1444,7 @@ int hcms_backward(hcms_ctx *ctx, const void *dout_seq, void *dq_seq, void *dk_se
         for (int i = 0; i < 12; ++i)
             if (!all[i]) return fail(HCMS_ERR_NULL, "a tensor pointer is NULL");
     int log2u = 0;
+    const int asked = mode;
     const int64_t ds_head = hcms::attention_backward_ds_head_bytes(S, d, dtype);
     const bool ds_path = ctx->ds != nullptr && ds_head > 0 && ctx->ds_region >= ds_head;
     if ((st = check_schedule(ctx, P, S, H, d, scale, chunk_sizes, n_chunks, dtype, &mode, &log2u,
@@ -1451,6 +1471,13 @@ int hcms_backward(hcms_ctx *ctx, const void *dout_seq, void *dq_seq, void *dk_se
         HCMS_OK)
         return st;
     if (S == 0) return ok();
+    // The path with stored score gradients takes as many heads at a time as a
+    // region holds: joined only where that is all of them.
+    if (asked == HCMS_MODE_AUTO && joins_chunks(ctx, S, H, d) &&
+        (!ds_path || ctx->ds_region >= ds_head * H)) {
+        chunk_sizes = &H;
+        n_chunks = 1;
+    }
 
     const int64_t head_bytes = static_cast<int64_t>(S) * d * elem_bytes(dtype);
     auto at = [head_bytes](const void *p, int h0) {
