@@ -1221,17 +1221,18 @@ int hcms_ctx_create(int device, int max_chunks, hcms_ctx **out) {
     {
         const int64_t slot = hcms::attention_split_slot_bytes();
         const int64_t n = 2 * int64_t{ctx->n_cu};
-        const int64_t region = n * slot + n * 4;
+        const int64_t region = n * slot, counts = n * 4;
         void *mem = nullptr;
-        if (hipMalloc(&mem, 2 * region) == hipSuccess && mem) {
-            if (hipMemset(mem, 0, 2 * region) == hipSuccess) {
+        if (hipMalloc(&mem, 2 * (region + counts)) == hipSuccess && mem) {
+            // Only the counters, behind both regions, have to start at zero.
+            char *const base = static_cast<char *>(mem);
+            if (hipMemset(base + 2 * region, 0, 2 * counts) == hipSuccess) {
                 ctx->split_mem = mem;
                 for (int r = 0; r < 2; ++r) {
-                    char *base = static_cast<char *>(mem) + r * region;
                     hcms::SplitScratch &sp = ctx->split[r];
-                    sp.part = base;
-                    sp.ml = base + n * (slot - 256 * 16);
-                    sp.count = reinterpret_cast<int *>(base + n * slot);
+                    sp.part = base + r * region;
+                    sp.ml = base + r * region + n * (slot - 256 * 16);
+                    sp.count = reinterpret_cast<int *>(base + 2 * region + r * counts);
                     sp.slots = static_cast<int>(n);
                     sp.counters = static_cast<int>(n);
                     sp.n_cu = ctx->n_cu;

@@ -103,10 +103,12 @@ __device__ inline void qk_mfma(f32x16 (&sacc)[NT][2], const __bf16 *ks,
 // O^T[dt][nt] += V^T[dt] P[nt]^T over the 64 keys of a block (4 k-steps of 16
 // keys); every V operand read from LDS feeds NT MFMAs.  The first kPvAhead
 // operands come in `pre` (read earlier by pv_prefetch), the others are read
-// kPvAhead MFMAs ahead of their use.  Two, not more: the kernel stays within
-// 248 VGPRs, so two waves per SIMD leave 16 registers per lane for the waves
-// of a pack or unpack running beside them.
-constexpr int kPvAhead = 2;
+// kPvAhead MFMAs ahead of their use.  With d = 128 two, not more: the kernel
+// stays within 248 VGPRs, so two waves per SIMD leave 16 registers per lane
+// for the waves of a pack or unpack running beside them.  With d = 64 four (16
+// heads of S = 8192 301 us with two, 295 with four or six, 303 with eight).
+template <int D>
+constexpr int kPvAhead = D == 64 ? 4 : 2;
 
 // Operand i = (ks, dt) = (i / DT, i % DT): consecutive MFMAs update different
 // O^T tiles, so none waits for the result of the one before it; each tile
@@ -118,21 +120,21 @@ __device__ inline const bf16x8 &vt_operand(const __bf16 *vts, int i, int li, int
 }
 
 template <int D>
-__device__ inline void pv_prefetch(bf16x8 (&pre)[kPvAhead], const __bf16 *vts, int li, int g) {
+__device__ inline void pv_prefetch(bf16x8 (&pre)[kPvAhead<D>], const __bf16 *vts, int li, int g) {
 #pragma unroll
-    for (int i = 0; i < kPvAhead; ++i) pre[i] = vt_operand<D>(vts, i, li, g);
+    for (int i = 0; i < kPvAhead<D>; ++i) pre[i] = vt_operand<D>(vts, i, li, g);
 }
 
 template <int D, int NT>
 __device__ inline void pv_mfma(f32x16 (&oacc)[D / 32][NT], const bf16x8 (&pb)[NT][4],
-                               const __bf16 *vts, const bf16x8 (&pre)[kPvAhead], int li, int g) {
+                               const __bf16 *vts, const bf16x8 (&pre)[kPvAhead<D>], int li, int g) {
     constexpr int N = 4 * (D / 32);
     bf16x8 a[N];
 #pragma unroll
-    for (int i = 0; i < kPvAhead; ++i) a[i] = pre[i];
+    for (int i = 0; i < kPvAhead<D>; ++i) a[i] = pre[i];
 #pragma unroll
     for (int i = 0; i < N; ++i) {
-        if (i + kPvAhead < N) a[i + kPvAhead] = vt_operand<D>(vts, i + kPvAhead, li, g);
+        if (i + kPvAhead<D> < N) a[i + kPvAhead<D>] = vt_operand<D>(vts, i + kPvAhead<D>, li, g);
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt)
             oacc[i % (D / 32)][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
@@ -160,7 +162,7 @@ __device__ inline void interleave_qk_exp() {
         }
         if (i + AHEAD < N) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
     }
-    __builtin_amdgcn_sched_group_barrier(0x100, kPvAhead, 0);  // V operand prefetch
+    __builtin_amdgcn_sched_group_barrier(0x100, kPvAhead<D>, 0);  // V operand prefetch
 }
 
 // Second half: the PV MFMAs with their V operand reads, and between them the
@@ -173,7 +175,7 @@ __device__ inline void interleave_pv_stage() {
     for (int i = 0; i < N; ++i) {
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
-        if (i + kPvAhead < N) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);            // DS read
+        if (i + kPvAhead<D> < N) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);            // DS read
         if (i >= 2) {
             __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);  // DS write
             __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);  // VALU
@@ -413,7 +415,7 @@ __global__ __launch_bounds__(64 * WAVES, PER_CU * WAVES / 4) void attention_kern
     };
     // Exponentials of one block, the per-query overflow test and, when some
     // query needs it, the recompute branch.
-    bf16x8 vpre[kPvAhead];
+    bf16x8 vpre[kPvAhead<D>];
     auto softmax = [&](const f32x16(&s)[NT][2], const __bf16 *vts) {
         float bsum[NT];
         bool up[NT], any_up = false;
