@@ -359,7 +359,8 @@ int hcms::auto_plan(int S, int d, int dtype, const int *sizes, int C, int n_cu, 
     // 0.02 us per key, for four synchronisations of 6 us and launches that
     // start later.  Below lanes_keys the plans without any are faster: two
     // chunks of S = 512 61 us in lanes, 36 serial; {4, 4} of S = 3001 88 in
-    // lanes, 78 fused (S = 32760 {5, 5}: lanes 4.3 ms, fused 4.7).
+    // lanes, 78 fused; but fp32 {3, 2} of S = 3075, d = 64, in two slots 95 in
+    // lanes, 126 serial (S = 32760 {5, 5}: lanes 4.3 ms, fused 4.7).
     const int64_t saved = rounds - (total + slots - 1) / slots;
     if (saved > 0 && saved * S >= lanes_keys) return HCMS_MODE_LANES;
     // The fused plan moves copies only on CUs a launch's last round leaves
@@ -368,13 +369,13 @@ int hcms::auto_plan(int S, int d, int dtype, const int *sizes, int C, int n_cu, 
     // The inline plan pays four synchronisations to run packs 1..C-1 beside
     // attention 0's last round: only worth it when that round has idle CUs
     // and lasts (S = 512: 85 us inline, 36 serial).
-    return first_idle && S >= lanes_keys ? HCMS_MODE_INLINE : HCMS_MODE_SERIAL;
+    return first_idle && S >= 4096 ? HCMS_MODE_INLINE : HCMS_MODE_SERIAL;
 }
 
 namespace {
 
 int auto_mode(int S, int d, int dtype, const int *sizes, int C, int n_cu) {
-    return hcms::auto_plan(S, d, dtype, sizes, C, n_cu, hcms::kForwardLanesKeys);
+    return hcms::auto_plan(S, d, dtype, sizes, C, n_cu, hcms::forward_lanes_keys(d, dtype));
 }
 
 // Saves the current device, switches to `dev`, restores on scope exit.
@@ -490,7 +491,7 @@ int check_schedule(hcms_ctx *ctx, int P, int S, int H, int d, float scale, const
         return fail(HCMS_ERR_ARG, "pipelined and slots modes need three distinct streams");
     int r = m != HCMS_MODE_AUTO ? m
             : hcms::auto_plan(S, d, dtype, chunk_sizes, n_chunks, ctx->n_cu,
-                              backward ? hcms::kBackwardLanesKeys : hcms::kForwardLanesKeys);
+                              backward ? hcms::kBackwardLanesKeys : hcms::forward_lanes_keys(d, dtype));
     // The backward with stored score gradients: one chunk's HBM-bound dQ
     // product overlaps the next chunk's key-parallel launch in lanes.
     if (m == HCMS_MODE_AUTO && prefer_lanes && n_chunks >= 2 && compute_stream != main_stream)

@@ -44,9 +44,11 @@ int attention_queries_per_block(int d);
 
 // The plan HCMS_MODE_AUTO runs for these chunks (hcms_auto_mode's rule; the
 // arguments are not validated).  lanes_keys: rounds saved * S from which on
-// the plans with synchronisations pay; a round of the backward lasts several
-// times as long as one of the forward.
-inline constexpr int64_t kForwardLanesKeys = 4096, kBackwardLanesKeys = 512;
+// lanes pay for their synchronisations; a round of the backward lasts several
+// times as long as one of the forward, and the kernels for d = 64 and for fp32
+// storage share no tiles, so that their partial rounds cost whole ones.
+inline constexpr int64_t kBackwardLanesKeys = 512;
+inline int64_t forward_lanes_keys(int d, int dtype) { return d == 128 && dtype == 0 ? 4096 : 1536; }
 int auto_plan(int S, int d, int dtype, const int *sizes, int C, int n_cu, int64_t lanes_keys);
 int attention_blocks_per_cu(int d);
 

@@ -690,14 +690,19 @@ def test_forward_slots_validation(lib):
 @pytest.mark.parametrize("S,d,sizes,want", [
     (512, 64, (2, 2), ("serial",) * 2),             # one round saved, of 512 keys
     (240, 64, (2, 2), ("serial",) * 2),
-    (3001, 128, (4, 4), ("fused", "serial")),       # 12 tiles: 1+1 > ceil(96/256) = 1; 3001 < 4096
+    (3001, 128, (4, 4), ("fused", "lanes")),        # 12 tiles: 1+1 > ceil(96/256) = 1
+    (1535, 128, (4, 4), ("fused", "serial")),
+    (1536, 128, (4, 4), ("fused", "lanes")),
+    (3075, 64, (3, 2), ("lanes",) * 2),
+    (1535, 64, (3, 2), ("serial",) * 2),
     (2048, 128, (1,) * 4, ("lanes",) * 2),          # 8 tiles each: 3 rounds saved, 6144
-    (4095, 128, (4, 4), ("fused", "serial")),
+    (4095, 128, (4, 4), ("fused", "lanes")),
     (4096, 128, (4, 4), ("lanes",) * 2),            # one round saved, of 4096 keys
     (4095, 64, (9, 16), ("serial",) * 2),           # 32 tiles, 512 slots: 1+1 = ceil(800/512); no inline
 ])
 def test_auto_mode_of_short_rounds(lib, S, d, sizes, want):
-    """Rounds saved * S below 4096: no plan with synchronisations."""
+    """Rounds saved * S below 4096 (d = 128 bf16) or 1536: no lanes; S below
+    4096: no inline plan."""
     modes = {"serial": hcms.MODE_SERIAL, "inline": hcms.MODE_INLINE, "lanes": hcms.MODE_LANES,
              "fused": hcms.MODE_FUSED}
     assert hcms.auto_mode(S, d, sizes, 256) == modes[want[0]]
