@@ -14,7 +14,7 @@
  * Conventions for every entry point
  *   - Buffers are device memory owned by the caller, contiguous, row-major,
  *     16-byte aligned.  The library allocates no device memory on any call
- *     except hcms_ctx_create (events, and 70 MiB to share tiles in).
+ *     except hcms_ctx_create (events, and 51 MiB to share tiles in).
  *   - `stream` arguments are hipStream_t handles passed as void*.  NULL is the
  *     null stream of the current device.  Streams are borrowed, never destroyed.
  *   - All compute calls are asynchronous and stream-ordered; a kernel fault
@@ -322,8 +322,10 @@ HCMS_API int hcms_plan(int n_chunks, int mode, hcms_op *ops, int cap);
  * ceil(sum_c W_c / (n_cu * B)).  A launch's last round leaves
  * n_cu * B * ceil(W_c / (n_cu * B)) - W_c slots idle.  Returns
  * HCMS_MODE_SERIAL for one chunk; HCMS_MODE_LANES when pooling saves rounds,
- * rounds saved * S >= 4096 (d = 128 with bf16 storage) or 1536 (shorter rounds
- * cost less than the lanes' synchronisations); otherwise, for d = 128 with bf16 storage, HCMS_MODE_FUSED when some launch
+ * rounds saved * S >= 8192 (d = 128 with bf16 storage, whose launches also
+ * share the tiles of their partial rounds: lanes only if part of a round is
+ * saved after that) or 1536 (shorter rounds cost less than the lanes'
+ * synchronisations); otherwise, for d = 128 with bf16 storage, HCMS_MODE_FUSED when some launch
  * leaves at least n_cu * B / 8 slots idle (where the neighbouring chunks'
  * copies ride) and HCMS_MODE_SERIAL when none does (the fused plan would run
  * the serial plan's launches); for the other kernels HCMS_MODE_INLINE when
@@ -542,7 +544,7 @@ HCMS_API int hcms_forward_slots(hcms_ctx *ctx, const void *q_seq, const void *k_
  * when the context's score-gradient workspace applies and there are two chunks
  * or more (one chunk's HBM-bound dQ product then overlaps the next chunk's
  * key-parallel launch), else what hcms_auto_mode picks with 512 in place of
- * 4096 and 1536 (its rounds last longer); it joins the chunks as hcms_forward does, with
+ * 8192 and 1536 (its rounds last longer); it joins the chunks as hcms_forward does, with
  * that workspace only if a region holds every head.  Every mode and
  * chunking gives bit-identical gradients.  Errors: as hcms_forward and
  * hcms_attention_backward.

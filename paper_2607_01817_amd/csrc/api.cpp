@@ -335,18 +335,20 @@ int plan_size(int C, int mode) {
 }  // namespace
 
 // The plan HCMS_MODE_AUTO runs (hcms_auto_mode without validation).
-int hcms::auto_plan(int S, int d, int dtype, const int *sizes, int C, int n_cu, int64_t lanes_keys) {
+int hcms::auto_plan(int S, int d, int dtype, const int *sizes, int C, int n_cu, bool backward) {
     if (C == 1) return HCMS_MODE_SERIAL;
     const int64_t br = hcms::attention_queries_per_block(d);
     const int64_t slots = static_cast<int64_t>(n_cu) * hcms::attention_blocks_per_cu(d);
     const int64_t tiles = (S + br - 1) / br;
     int64_t rounds = 0, total = 0;
+    double shared = 0;            // rounds, partial ones as long as sharing leaves them
     bool some_idle = false;       // a launch whose last round leaves enough slots idle
     bool first_idle = false;      // ... for chunk 0's launch in particular
     for (int c = 0; c < C; ++c) {
         const int64_t wc = tiles * sizes[c];
         rounds += (wc + slots - 1) / slots;
         total += wc;
+        shared += wc / slots + hcms::attention_partial_round(wc % slots, S, n_cu);
         // The workgroups the launch runs: its last round's tiles may be split.
         const int64_t rem = wc % slots;
         const int64_t run = wc - rem + rem * hcms::attention_split_ways(wc, S, d, dtype, n_cu);
@@ -359,10 +361,18 @@ int hcms::auto_plan(int S, int d, int dtype, const int *sizes, int C, int n_cu, 
     // 0.02 us per key, for four synchronisations of 6 us and launches that
     // start later.  Below lanes_keys the plans without any are faster: two
     // chunks of S = 512 61 us in lanes, 36 serial; {4, 4} of S = 3001 88 in
-    // lanes, 78 fused; but fp32 {3, 2} of S = 3075, d = 64, in two slots 95 in
+    // lanes, 78 fused, {5, 4, 4} of S = 6000 326 and 303; but fp32 {3, 2} of S = 3075, d = 64, in two slots 95 in
     // lanes, 126 serial (S = 32760 {5, 5}: lanes 4.3 ms, fused 4.7).
+    // Where the kernel shares the tiles of its partial rounds, lanes have to
+    // save a part of a round after that too: {2, 2, 2, 2} of S = 9610, 4
+    // thirds of a round either way, 483 us in lanes, 419 fused.  The backward
+    // shares none, and its rounds last several times as long.
     const int64_t saved = rounds - (total + slots - 1) / slots;
-    if (saved > 0 && saved * S >= lanes_keys) return HCMS_MODE_LANES;
+    const bool shares = !backward && d == 128 && dtype == HCMS_BF16;
+    const int64_t lanes_keys = backward ? 512 : shares ? 8192 : 1536;
+    if (saved > 0 && saved * S >= lanes_keys &&
+        (!shares || shared > total / slots + hcms::attention_partial_round(total % slots, S, n_cu) + 0.01))
+        return HCMS_MODE_LANES;
     // The fused plan moves copies only on CUs a launch's last round leaves
     // idle; with none anywhere it would run the serial plan's launches.
     if (d == 128 && dtype == HCMS_BF16) return some_idle ? HCMS_MODE_FUSED : HCMS_MODE_SERIAL;
@@ -375,7 +385,7 @@ int hcms::auto_plan(int S, int d, int dtype, const int *sizes, int C, int n_cu, 
 namespace {
 
 int auto_mode(int S, int d, int dtype, const int *sizes, int C, int n_cu) {
-    return hcms::auto_plan(S, d, dtype, sizes, C, n_cu, hcms::forward_lanes_keys(d, dtype));
+    return hcms::auto_plan(S, d, dtype, sizes, C, n_cu);
 }
 
 // Saves the current device, switches to `dev`, restores on scope exit.
@@ -490,8 +500,7 @@ int check_schedule(hcms_ctx *ctx, int P, int S, int H, int d, float scale, const
         (copy_stream == compute_stream || copy_stream == main_stream || compute_stream == main_stream))
         return fail(HCMS_ERR_ARG, "pipelined and slots modes need three distinct streams");
     int r = m != HCMS_MODE_AUTO ? m
-            : hcms::auto_plan(S, d, dtype, chunk_sizes, n_chunks, ctx->n_cu,
-                              backward ? hcms::kBackwardLanesKeys : hcms::forward_lanes_keys(d, dtype));
+            : hcms::auto_plan(S, d, dtype, chunk_sizes, n_chunks, ctx->n_cu, backward);
     // The backward with stored score gradients: one chunk's HBM-bound dQ
     // product overlaps the next chunk's key-parallel launch in lanes.
     if (m == HCMS_MODE_AUTO && prefer_lanes && n_chunks >= 2 && compute_stream != main_stream)
@@ -726,11 +735,10 @@ int issue_forward(const ForwardArgs &args, int mode, int log2u) {
     auto split_for = [&](hipStream_t s, int c) -> const hcms::SplitScratch * {
         const int r = s == static_cast<hipStream_t>(f.main_stream) ? 0
                       : s == static_cast<hipStream_t>(f.compute_stream) ? 1 : -1;
-        if (r < 0 || !f.ctx->split[r].part) return nullptr;
-        if (mode != HCMS_MODE_LANES) return &f.ctx->split[r];
-        if (c < f.n_chunks - 2) return nullptr;
+        if (r < 0) return nullptr;
+        if (mode != HCMS_MODE_LANES || f.n_chunks < 2) return &f.ctx->split[r];
         lanes_tail = f.ctx->split[r];
-        lanes_tail.tail = pooled % f.ctx->n_cu;
+        lanes_tail.tail = c < f.n_chunks - 2 ? 0 : pooled % f.ctx->n_cu;
         return &lanes_tail;
     };
     auto launch = [&](int kind, int c, int h0, int hc, hipStream_t s) -> hipError_t {
@@ -1217,25 +1225,26 @@ int hcms_ctx_create(int device, int max_chunks, hcms_ctx **out) {
         }
         ctx->events.push_back(ev);
     }
-    // Split scratch, two regions of 2 n_cu slots and as many counters each.  If
-    // it cannot be had, launches split no tile by segments (same results).
+    // Split scratch: two regions, of 2 n_cu slots for launches on the main
+    // stream and n_cu for those on the compute stream, with as many counters.
+    // If it cannot be had, launches split no tile by segments (same results).
     {
         const int64_t slot = hcms::attention_split_slot_bytes();
-        const int64_t n = 2 * int64_t{ctx->n_cu};
-        const int64_t region = n * slot, counts = n * 4;
+        const int64_t slots[2] = {2 * int64_t{ctx->n_cu}, ctx->n_cu}, all = slots[0] + slots[1];
         void *mem = nullptr;
-        if (hipMalloc(&mem, 2 * (region + counts)) == hipSuccess && mem) {
+        if (hipMalloc(&mem, all * (slot + 4)) == hipSuccess && mem) {
             // Only the counters, behind both regions, have to start at zero.
             char *const base = static_cast<char *>(mem);
-            if (hipMemset(base + 2 * region, 0, 2 * counts) == hipSuccess) {
+            if (hipMemset(base + all * slot, 0, all * 4) == hipSuccess) {
                 ctx->split_mem = mem;
                 for (int r = 0; r < 2; ++r) {
+                    const int64_t first = r == 0 ? 0 : slots[0];
                     hcms::SplitScratch &sp = ctx->split[r];
-                    sp.part = base + r * region;
-                    sp.ml = base + r * region + n * (slot - 256 * 16);
-                    sp.count = reinterpret_cast<int *>(base + 2 * region + r * counts);
-                    sp.slots = static_cast<int>(n);
-                    sp.counters = static_cast<int>(n);
+                    sp.part = base + first * slot;
+                    sp.ml = base + first * slot + slots[r] * (slot - 256 * 16);
+                    sp.count = reinterpret_cast<int *>(base + all * slot + first * 4);
+                    sp.slots = static_cast<int>(slots[r]);
+                    sp.counters = static_cast<int>(slots[r]);
                     sp.n_cu = ctx->n_cu;
                 }
             } else {

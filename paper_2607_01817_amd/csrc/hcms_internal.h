@@ -43,13 +43,8 @@ inline constexpr unsigned kCopyBesideAttentionLds = 40 * 1024;
 int attention_queries_per_block(int d);
 
 // The plan HCMS_MODE_AUTO runs for these chunks (hcms_auto_mode's rule; the
-// arguments are not validated).  lanes_keys: rounds saved * S from which on
-// lanes pay for their synchronisations; a round of the backward lasts several
-// times as long as one of the forward, and the kernels for d = 64 and for fp32
-// storage share no tiles, so that their partial rounds cost whole ones.
-inline constexpr int64_t kBackwardLanesKeys = 512;
-inline int64_t forward_lanes_keys(int d, int dtype) { return d == 128 && dtype == 0 ? 4096 : 1536; }
-int auto_plan(int S, int d, int dtype, const int *sizes, int C, int n_cu, int64_t lanes_keys);
+// arguments are not validated), or for the backward of these chunks.
+int auto_plan(int S, int d, int dtype, const int *sizes, int C, int n_cu, bool backward = false);
 int attention_blocks_per_cu(int d);
 
 // Scratch for splitting a launch's last round of tiles over several
@@ -74,6 +69,9 @@ int64_t attention_split_slot_bytes();
 // tiles, shared by so many workgroups each, fit in one round, else 1.  (The
 // launch itself may share them further: halves of a tile, two rounds.)
 int attention_split_ways(int64_t W, int S, int d, int dtype, int n_cu);
+// About how long a d = 128 bf16 launch's last round of t < n_cu tiles takes,
+// in rounds, with the tiles shared as the launch does.
+double attention_partial_round(int64_t t, int S, int n_cu);
 
 // lse, if not NULL, receives [n_heads][S] fp32 log2 softmax denominators:
 // P_ij = exp2(scale_log2e * <q_i, k_j> - lse_i).  split: NULL, or scratch

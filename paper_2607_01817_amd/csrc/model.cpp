@@ -168,7 +168,7 @@ int hcms_model_plan_time(int S, int d, int dtype, const int *chunk_sizes, int n_
         int64_t H = 0;
         for (int c = 0; c < n_chunks; ++c) H += chunk_sizes[c];
         if (H > 0x7fffffff) return hcms::fail(HCMS_ERR_CHUNKS, "too many heads");
-        mode = hcms::auto_plan(S, d, dtype, chunk_sizes, n_chunks, n_cu, hcms::forward_lanes_keys(d, dtype));
+        mode = hcms::auto_plan(S, d, dtype, chunk_sizes, n_chunks, n_cu);
     }
     if (!plan_mode(mode)) return hcms::fail(HCMS_ERR_ARG, "mode %d is not a plan", mode);
     *t_out = plan_time(S, d, dtype, chunk_sizes, n_chunks, mode, n_cu, t_round, g0, drain, t_copy,
@@ -191,7 +191,7 @@ int hcms_choose_chunks(int S, int H, int d, int dtype, int n_cu, double t_round,
     int best_mode = HCMS_MODE_SERIAL;
     for (int C = 1; C <= top; ++C) {
         for (int c = 0; c < C; ++c) sizes[c] = H / C + (c < H % C ? 1 : 0);
-        const int mode = hcms::auto_plan(S, d, dtype, sizes.data(), C, n_cu, hcms::forward_lanes_keys(d, dtype));
+        const int mode = hcms::auto_plan(S, d, dtype, sizes.data(), C, n_cu);
         const double t = plan_time(S, d, dtype, sizes.data(), C, mode, n_cu, t_round, g0, drain,
                                    t_copy, beta);
         if (t < best_t) {   // ties keep the smaller chunk count

@@ -695,14 +695,16 @@ def test_forward_slots_validation(lib):
     (1536, 128, (4, 4), ("fused", "lanes")),
     (3075, 64, (3, 2), ("lanes",) * 2),
     (1535, 64, (3, 2), ("serial",) * 2),
-    (2048, 128, (1,) * 4, ("lanes",) * 2),          # 8 tiles each: 3 rounds saved, 6144
+    (2048, 128, (1,) * 4, ("fused", "lanes")),      # 8 tiles each: 3 rounds saved, 6144
     (4095, 128, (4, 4), ("fused", "lanes")),
-    (4096, 128, (4, 4), ("lanes",) * 2),            # one round saved, of 4096 keys
+    (8191, 128, (4, 4), ("serial", "lanes")),       # 128 tiles each: one round saved, none idle
+    (8192, 128, (4, 4), ("lanes",) * 2),            # 0.75 each, shared; pooled one round
+    (9610, 128, (2,) * 4, ("serial", "lanes")),     # 76 tiles each, 0.33 shared; pooled 1.33
     (4095, 64, (9, 16), ("serial",) * 2),           # 32 tiles, 512 slots: 1+1 = ceil(800/512); no inline
 ])
 def test_auto_mode_of_short_rounds(lib, S, d, sizes, want):
-    """Rounds saved * S below 4096 (d = 128 bf16) or 1536: no lanes; S below
-    4096: no inline plan."""
+    """Rounds saved * S below 8192 (d = 128 bf16, and nothing saved with shared
+    tiles) or 1536: no lanes; S below 4096: no inline plan."""
     modes = {"serial": hcms.MODE_SERIAL, "inline": hcms.MODE_INLINE, "lanes": hcms.MODE_LANES,
              "fused": hcms.MODE_FUSED}
     assert hcms.auto_mode(S, d, sizes, 256) == modes[want[0]]
