@@ -913,7 +913,7 @@ __global__ __launch_bounds__(64 * dma::kWaves, dma::kWaves / 4) void attention_d
     const int g = lane >> 5;
     const int q0 = qbase + wave * kQW;
     // A wave without queries (past S, or the other half's) only loads: then
-    // the wave it shares a SIMD with runs a step in about 0.56 of the time.
+    // the wave it shares a SIMD with runs a step in about 0.65 of the time.
     const bool computes = q0 < S && (half < 0 || wave < kWaves / 2);
 
     bf16x8 qreg[KK];

@@ -34,8 +34,8 @@
 //     over the next one, and the MFMAs behind it need neither.  Before, the
 //     operand reads followed the barrier and the blocks passed through
 //     registers: 8192 x 8192 x 8192 took 925 us (1188 TFLOP/s), 56160 x 1920 x
-//     5120 1056, 56160 x 5120 x 640 406; on the same card now 793, 923 and
-//     345.  What bounds it now: the power limit (1.7 GHz with the matrix
+//     5120 1056, 56160 x 5120 x 640 406; now 797, 942 and
+//     352.  What bounds it now: the power limit (1.7 GHz with the matrix
 //     cores 75 % busy; without any load it would run 8 % faster, an MFMA loop
 //     with the same LDS reads on random operands reaches 1710 TFLOP/s);
 //   * tiles are ordered in groups of 8 row tiles (all column tiles of a group
