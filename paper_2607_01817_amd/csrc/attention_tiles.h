@@ -59,16 +59,18 @@ __device__ inline void store4(float *p, f32x4 x) { *reinterpret_cast<f32x4 *>(p)
 // zeros) land at LDS byte lds_addr + 16 l.  Inline asm: with the intrinsic the
 // compiler waits for every such load before any later LDS read, so the
 // kernels count these loads themselves (wait_vm).  M0 is written here and read
-// by nothing else in the kernels.
+// by nothing else in the kernels.  s_nop: an instruction that reads M0 needs a
+// wait state after a scalar write of it, which the compiler puts only between
+// instructions of its own.
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
 __device__ inline void load_lds(unsigned lds_addr, __amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff) {
-    asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
                  :: "s"(lds_addr), "v"(voff), "s"(r), "s"(soff) : "memory", "m0");
 }
 // The same with 4 bytes per lane (lane l at LDS byte lds_addr + 4 l).
 __device__ inline void load_lds_b32(unsigned lds_addr, __amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff) {
-    asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dword %1, %2, %3 offen lds"
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, %3 offen lds"
                  :: "s"(lds_addr), "v"(voff), "s"(r), "s"(soff) : "memory", "m0");
 }
 #pragma clang diagnostic pop
