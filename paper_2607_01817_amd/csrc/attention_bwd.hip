@@ -60,6 +60,7 @@
 #include <algorithm>
 
 #include "attention_tiles.h"
+#include "buffer_store.h"
 #include "hcms_internal.h"
 
 namespace hcms {
@@ -746,10 +747,8 @@ __global__ __launch_bounds__(64 * bdma::kWaves, bdma::kWaves / 4) void attention
             // Through a buffer resource over the 8 tiles of this key tile
             // (scalar base and offset): no 64-bit lane addresses.
             const __amdgpu_buffer_rsrc_t dr = head_rsrc(ds_wave + (i >> 3) * ds_step, kDsGroupB);
-            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, dsb[0]), dr, ds_lane,
-                                                   (i & 7) * kDsTileB, 0);
-            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, dsb[1]), dr,
-                                                   ds_lane + 1024, (i & 7) * kDsTileB, 0);
+            store_b128(__builtin_bit_cast(u32x4, dsb[0]), dr, ds_lane, (i & 7) * kDsTileB);
+            store_b128(__builtin_bit_cast(u32x4, dsb[1]), dr, ds_lane + 1024, (i & 7) * kDsTileB);
         }
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt)

@@ -17,6 +17,8 @@
 
 #include <cstdint>
 
+#include "buffer_store.h"
+
 namespace hcms {
 namespace copy {
 
@@ -80,7 +82,7 @@ __device__ inline void copy_block(const PackPtrs &p, int64_t S, int64_t H, int64
             buf[i] = __builtin_amdgcn_raw_buffer_load_b128(src, so, i * step, kNonTemporal);
 #pragma unroll
         for (int i = 0; i < kUnroll; ++i)
-            __builtin_amdgcn_raw_buffer_store_b128(buf[i], dst, tid << 4, i * (kThreads << 4), 0);
+            store_b128(buf[i], dst, tid << 4, i * (kThreads << 4));
     } else {
         const __amdgpu_buffer_rsrc_t src = span_rsrc(p.src[z] + b.dense_off, b.dense_left);
         const __amdgpu_buffer_rsrc_t dst = span_rsrc(p.dst[z] + b.strided_off, b.strided_left);
@@ -90,7 +92,7 @@ __device__ inline void copy_block(const PackPtrs &p, int64_t S, int64_t H, int64
                                                            kNonTemporal);
 #pragma unroll
         for (int i = 0; i < kUnroll; ++i)
-            __builtin_amdgcn_raw_buffer_store_b128(buf[i], dst, so, i * step, 0);
+            store_b128(buf[i], dst, so, i * step);
     }
 }
 

@@ -56,3 +56,27 @@ def test_m0_is_not_read_right_after_its_write(kernels):
             seen += 1
             assert not re.match(r"s_\w+ m0,", ins[i - 1]), f"{src}: {ins[i - 1]} / {ins[i]}"
     assert seen > 100   # the check looks at the loads that it is about
+
+
+def _vgprs(operand):
+    m = re.match(r"v\[(\d+):(\d+)\]$|v(\d+)$", operand)
+    if not m:
+        return set()
+    lo, hi = (m[1], m[2]) if m[1] else (m[3], m[3])
+    return set(range(int(lo), int(hi) + 1))
+
+
+def test_wide_stores_keep_their_data_for_a_wait_state(kernels):
+    """A store of more than 8 bytes per lane reads its data registers after it
+    has issued, with a scalar offset too: the instruction behind it does not
+    write them."""
+    seen = 0
+    for src, ins in kernels.items():
+        for st, after in zip(ins, ins[1:]):
+            if not re.match(r"buffer_store_dwordx[34] .*, s\d+ offen", st):
+                continue
+            seen += 1
+            data = _vgprs(st.split(None, 1)[1].split(",")[0])
+            written = _vgprs(after.partition(" ")[2].split(",")[0]) if re.match(r"(v|ds)_", after) else set()
+            assert data and not data & written, f"{src}: {st} / {after}"
+    assert seen > 10
