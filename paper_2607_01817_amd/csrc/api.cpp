@@ -461,7 +461,7 @@ struct hcms_ctx {
     // Scratch that lets an attention launch split its last round of tiles:
     // one region for launches on the main stream, one for the compute stream
     // (launches on one stream are ordered, so each region serves one launch
-    // at a time).  No region: every tile whole, with the same results.
+    // at a time).  Empty regions: no tile split by segments, the same results.
     void *split_mem = nullptr;
     hcms::SplitScratch split[2] = {};
     // Caller-owned score-gradient workspace of hcms_backward: two regions of
@@ -1225,33 +1225,20 @@ int hcms_ctx_create(int device, int max_chunks, hcms_ctx **out) {
         }
         ctx->events.push_back(ev);
     }
-    // Split scratch: two regions, of 2 n_cu slots for launches on the main
-    // stream and n_cu for those on the compute stream, with as many counters.
-    // If it cannot be had, launches split no tile by segments (same results).
+    // Split scratch: a region for launches on the main stream and one for
+    // those on the compute stream.  If it cannot be had, the regions are empty.
     {
         const int64_t slot = hcms::attention_split_slot_bytes();
-        const int64_t slots[2] = {2 * int64_t{ctx->n_cu}, ctx->n_cu}, all = slots[0] + slots[1];
+        const int64_t bytes = hcms::split_bytes(ctx->n_cu, slot), zero = hcms::split_counter_bytes(ctx->n_cu);
         void *mem = nullptr;
-        if (hipMalloc(&mem, all * (slot + 4)) == hipSuccess && mem) {
-            // Only the counters, behind both regions, have to start at zero.
-            char *const base = static_cast<char *>(mem);
-            if (hipMemset(base + all * slot, 0, all * 4) == hipSuccess) {
-                ctx->split_mem = mem;
-                for (int r = 0; r < 2; ++r) {
-                    const int64_t first = r == 0 ? 0 : slots[0];
-                    hcms::SplitScratch &sp = ctx->split[r];
-                    sp.part = base + first * slot;
-                    sp.ml = base + first * slot + slots[r] * (slot - 256 * 16);
-                    sp.count = reinterpret_cast<int *>(base + all * slot + first * 4);
-                    sp.slots = static_cast<int>(slots[r]);
-                    sp.counters = static_cast<int>(slots[r]);
-                    sp.n_cu = ctx->n_cu;
-                }
-            } else {
-                (void)hipFree(mem);
-            }
+        if (hipMalloc(&mem, bytes) != hipSuccess) mem = nullptr;
+        if (mem && hipMemset(static_cast<char *>(mem) + (bytes - zero), 0, zero) != hipSuccess) {
+            (void)hipFree(mem);
+            mem = nullptr;
         }
         (void)hipGetLastError();
+        ctx->split_mem = mem;
+        for (int r = 0; r < 2; ++r) ctx->split[r] = hcms::split_region(mem, r, ctx->n_cu, slot);
     }
     *out = ctx;
     return ok();

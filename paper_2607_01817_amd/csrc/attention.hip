@@ -555,8 +555,8 @@ static_assert(kPerWave == 2, "the wait counts below assume two DMA instructions 
 // arithmetic of a query never depends on which workgroups computed which
 // segments: a tile may be computed whole by one workgroup or split over
 // several, with bit-identical results.
-constexpr int kSeg = 3;
-constexpr int kSegMinBlocks = 12;
+constexpr int kSeg = kKeySegments;
+constexpr int kSegMinBlocks = kKeySegmentMinBlocks;
 __host__ __device__ inline int n_segments(int nkb) { return nkb >= kSegMinBlocks ? kSeg : 1; }
 // First block of segment g (g = n_segments: one past the last block).
 __host__ __device__ inline int seg_begin(int nkb, int g) {
@@ -719,27 +719,6 @@ __device__ inline void run_riders(const Riders &r, unsigned rider, unsigned n_ri
             copy::copy_block<kRiderLog2U, false>(jb.p, r.S, r.H, jb.h0, x, j, z, t);
     }
 }
-
-// Tiles shared by several workgroups (the launch's last, partial round of
-// tiles; see plan_split).  Of the `units` = n_split * halves * ways workgroups
-// after the whole tiles', workgroup u takes part u % parts, parts = n_split *
-// halves: with halves = 2 the first or second 128 queries of tile n_whole +
-// part / 2, else the whole tile n_whole + part; and of it with ways = 3 key
-// segment u / parts, with ways = 1 all of them.  With 3 ways each writes its
-// partial state (the normalised output in the stash layout, and (m, l, E) per
-// query) to slot u and counts itself in on its part's counter; the last to
-// arrive merges the part's states in segment order, writes the output and
-// sets the counter back to zero.
-struct TailSplit {
-    char *part;      // units slots of kStashB bytes (ways = 3)
-    float4 *ml;      // units slots of 256 (m, l, E, 0) per query
-    int *count;      // a counter per part, zero between launches
-    int n_whole;     // tiles computed whole by one workgroup: the first n_whole
-    int n_split;     // tiles split: the last n_split
-    int halves;      // 1 or 2
-    int ways;        // 1 or 3
-    int units() const { return n_split * halves * ways; }
-};
 
 // The state of a query after some of its key segments: the maximum m of its
 // raw scores, the row sum l of exp2(c (s - m)), and the normalised output N
@@ -1194,7 +1173,8 @@ __global__ __launch_bounds__(64 * dma::kWaves, dma::kWaves / 4) void attention_d
                                 static_cast<unsigned>(wave * kStashWaveB + 16 * lane2)};
         };
         const auto stats = [&](int slot) {
-            return head_rsrc(tail.ml + static_cast<int64_t>(slot) * (kWaves * kQW), kWaves * kQW * sizeof(float4));
+            constexpr int64_t kBytes = kWaves * kQW * sizeof(float4);
+            return head_rsrc(tail.ml + slot * kBytes, kBytes);
         };
         const unsigned stat_off = (wave * kQW + li2) * sizeof(float4);
         if (computes) {
@@ -1274,44 +1254,6 @@ struct Shape {
     static constexpr int PER_CU = D == 128 ? 1 : 2;   // workgroups one CU holds
 };
 
-// The split of a d = 128 bf16 launch of W tiles on n_cu CUs (one workgroup
-// per CU): the last round's t = W mod n_cu tiles are shared by more workgroups
-// where that shortens it.  In rounds, of which a whole tile takes 1:
-//   three key segments of halves of 128 queries   0.25, and 4 us to merge
-//   three key segments                            0.33, and 4 us
-//   halves (half the waves only load)             0.65, to 0.85 with every CU busy
-//   three key segments in two rounds              0.67, and 4 us
-// and the first that fits is taken, in this order: 64 tiles of S = 4096 take
-// 92 us whole, 64 in halves, 38 in thirds; 128 tiles 92, 79 and, in thirds
-// over two rounds, 88; 155 tiles of S = 7800 165 and 145.  Segments need
-// scratch (none: halves or whole tiles, the same
-// results).  With sp->tail >= 0, t is that and the last
-// min(tail, W) tiles are split: a launch whose last round is shared with
-// another stream's launch splits the tiles that close the pooled rounds.
-TailSplit plan_split(int64_t W, int S, int n_cu, const SplitScratch *sp) {
-    TailSplit p{nullptr, nullptr, nullptr, static_cast<int>(W), 0, 1, 1};
-    const int nkb = (S + kBC - 1) / kBC;
-    const int64_t n = n_cu, t = sp && sp->tail >= 0 ? sp->tail : W % n, rem = std::min(t, W);
-    if (n < 2 || rem == 0) return p;
-    auto scratch = [&](int halves) {
-        return sp && sp->part && dma::n_segments(nkb) == dma::kSeg && rem * halves * dma::kSeg <= sp->slots &&
-               rem * halves <= sp->counters;
-    };
-    if (6 * t <= n && scratch(2)) p.halves = 2, p.ways = 3;
-    else if (3 * t <= n && scratch(1)) p.ways = 3;
-    else if (2 * t <= n) p.halves = 2;
-    else if (3 * t <= 2 * n && scratch(1)) p.ways = 3;
-    else return p;
-    if (p.ways > 1) {
-        p.part = static_cast<char *>(sp->part);
-        p.ml = static_cast<float4 *>(sp->ml);
-        p.count = sp->count;
-    }
-    p.n_whole = static_cast<int>(W - rem);
-    p.n_split = static_cast<int>(rem);
-    return p;
-}
-
 // Compute units of the current device.
 hipError_t current_cus(int *n_cu) {
     int device = 0;
@@ -1332,7 +1274,7 @@ hipError_t launch_typed(const void *q, const void *k, const void *v, void *o, fl
         int n_cu = split ? split->n_cu : 0;
         if (!split)
             if (const hipError_t e = current_cus(&n_cu); e != hipSuccess) return e;
-        const TailSplit t = plan_split(blocks, S, n_cu, split);
+        const TailSplit t = plan_split(blocks, (S + kBC - 1) / kBC, n_cu, split);
         const int64_t grid = static_cast<int64_t>(t.n_whole) + t.units();
         if (grid > 0x7fffffff) return hipErrorInvalidValue;
         attention_dma_kernel<false><<<static_cast<unsigned>(grid), 64 * dma::kWaves, 0, stream>>>(
@@ -1351,7 +1293,7 @@ hipError_t launch_typed(const void *q, const void *k, const void *v, void *o, fl
 int attention_queries_per_block(int d) { return d == 128 ? Shape<128>::BR : Shape<64>::BR; }
 int attention_blocks_per_cu(int d) { return d == 128 ? Shape<128>::PER_CU : Shape<64>::PER_CU; }
 
-int64_t attention_split_slot_bytes() { return dma::kStashB + 256 * int64_t{sizeof(float4)}; }
+int64_t attention_split_slot_bytes() { return dma::kStashB + 256 * int64_t{sizeof(float4)}; }   // ml: 4 KiB
 
 int attention_split_ways(int64_t W, int S, int d, int dtype, int n_cu) {
     if (!(kLdsDma && d == dma::kD && dtype == 0)) return 1;
@@ -1366,7 +1308,7 @@ double attention_partial_round(int64_t t, int S, int n_cu) {
     sp.part = sp.ml = reinterpret_cast<void *>(uintptr_t{256});   // placeholders: never dereferenced
     sp.n_cu = n_cu;
     sp.slots = sp.counters = 2 * n_cu;
-    const TailSplit p = plan_split(t, S, n_cu, &sp);
+    const TailSplit p = plan_split(t, (S + kBC - 1) / kBC, n_cu, &sp);
     if (p.ways == 3) return p.halves == 2 ? 0.25 : 3 * t <= n_cu ? 0.33 : 0.67;
     return p.halves == 2 ? 0.75 : 1;
 }
@@ -1397,7 +1339,7 @@ hipError_t launch_attention_riding(const void *q, const void *k, const void *v, 
         return launch_attention(q, k, v, o, lse, S, n_heads, d, scale_log2e, dtype, split, stream);
     using Sh = Shape<dma::kD>;
     const int64_t n_qtiles = (S + Sh::BR - 1) / Sh::BR;
-    const TailSplit t = plan_split(n_qtiles * n_heads, S, n_cu, split);
+    const TailSplit t = plan_split(n_qtiles * n_heads, (S + kBC - 1) / kBC, n_cu, split);
     const int64_t n_attn = static_cast<int64_t>(t.n_whole) + t.units();
     const int64_t idle = (n_cu - n_attn % n_cu) % n_cu;
     Riders r{};

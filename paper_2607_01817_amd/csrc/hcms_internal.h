@@ -5,6 +5,8 @@
 
 #include <cstdint>
 
+#include "split_plan.h"
+
 namespace hcms {
 
 // Thread-local error detail behind hcms_last_error: fail() records a message
@@ -47,22 +49,7 @@ int attention_queries_per_block(int d);
 int auto_plan(int S, int d, int dtype, const int *sizes, int C, int n_cu, bool backward = false);
 int attention_blocks_per_cu(int d);
 
-// Scratch for splitting a launch's last round of tiles over several
-// workgroups (d = 128 bf16): `slots` partial states of
-// attention_split_slot_bytes() bytes each (part: slots x 64 KiB, ml: slots x
-// 4 KiB, 16-byte aligned) and `counters` ints that are zero between launches.  At most one
-// launch may use one scratch at a time (launches on one stream are ordered).
-struct SplitScratch {
-    void *part;
-    void *ml;
-    int *count;
-    int slots, counters;
-    int n_cu;
-    // Tiles at the end of the launch to split: -1 for the launch's own last
-    // round (W mod n_cu); otherwise this many (at most W), for a launch whose
-    // last tiles close a round that other launches' workgroups share.
-    int64_t tail = -1;
-};
+// Bytes of a partial state of SplitScratch (split_plan.h).
 int64_t attention_split_slot_bytes();
 // Workgroups per split tile of the time model and of the mode rule, for a
 // launch of W tiles on n_cu CUs: 3 or 2 where the last round's W mod n_cu

@@ -1,0 +1,118 @@
+// How a d = 128 bf16 attention launch shares its last tiles, and the scratch
+// that it shares them in.  Plain C++, no HIP: host rules and host tests use it
+// as the kernels' launchers do.
+#pragma once
+
+#include <algorithm>
+#include <cstdint>
+
+namespace hcms {
+
+// Every query visits its keys as kKeySegments fixed segments of whole key
+// blocks, or as one where there are fewer than kKeySegmentMinBlocks blocks.
+inline constexpr int kKeySegments = 3;
+inline constexpr int kKeySegmentMinBlocks = 12;
+
+// Scratch for splitting a launch's last round of tiles over several
+// workgroups (d = 128 bf16): `slots` partial states of
+// attention_split_slot_bytes() bytes each (part: slots x 64 KiB, ml: slots x
+// 4 KiB, 16-byte aligned) and `counters` ints that are zero between launches.
+// part NULL: none, and no tile is split by segments.  At most one launch may
+// use one scratch at a time (launches on one stream are ordered).
+struct SplitScratch {
+    void *part;
+    void *ml;
+    int *count;
+    int slots, counters;
+    int n_cu;
+    // Tiles at the end of the launch to split: -1 for the launch's own last
+    // round (W mod n_cu); otherwise this many (at most W), for a launch whose
+    // last tiles close a round that other launches' workgroups share.
+    int64_t tail = -1;
+};
+
+// The scratch of launches on the main stream (r = 0: 2 n_cu slots) and on the
+// compute stream (r = 1: n_cu), as many counters each.
+inline int split_slots(int r, int n_cu) { return r == 0 ? 2 * n_cu : n_cu; }
+inline int64_t split_slots_all(int n_cu) { return int64_t{split_slots(0, n_cu)} + split_slots(1, n_cu); }
+// Bytes of all of it with states of slot_bytes (4 KiB of them for ml), and
+// their part that has to start at zero: the counters, at the end.
+inline int64_t split_bytes(int n_cu, int64_t slot_bytes) { return split_slots_all(n_cu) * (slot_bytes + 4); }
+inline int64_t split_counter_bytes(int n_cu) { return split_slots_all(n_cu) * 4; }
+// Region r of it; mem NULL (none could be had): an empty scratch, with which
+// launches split no tile by segments and give the same results.
+inline SplitScratch split_region(void *mem, int r, int n_cu, int64_t slot_bytes) {
+    SplitScratch s{};
+    s.n_cu = n_cu;
+    if (!mem) return s;
+    char *const base = static_cast<char *>(mem);
+    const int64_t first = r == 0 ? 0 : split_slots(0, n_cu);
+    s.slots = s.counters = split_slots(r, n_cu);
+    s.part = base + first * slot_bytes;
+    s.ml = base + first * slot_bytes + s.slots * (slot_bytes - 4096);
+    s.count = reinterpret_cast<int *>(base + split_slots_all(n_cu) * slot_bytes + first * 4);
+    return s;
+}
+
+// Tiles shared by several workgroups (the launch's last, partial round of
+// tiles; see plan_split).  Of the `units` = n_split * halves * ways workgroups
+// after the whole tiles', workgroup u takes part u % parts, parts = n_split *
+// halves: with halves = 2 the first or second 128 queries of tile n_whole +
+// part / 2, else the whole tile n_whole + part; and of it with ways = 3 key
+// segment u / parts, with ways = 1 all of them.  With 3 ways each writes its
+// partial state (the normalised output in the stash layout, and (m, l, E) per
+// query) to slot u and counts itself in on its part's counter; the last to
+// arrive merges the part's states in segment order, writes the output and
+// sets the counter back to zero.
+struct TailSplit {
+    char *part;      // units slots of 64 KiB (ways = 3)
+    char *ml;        // units slots of 256 (m, l, E, 0) per query
+    int *count;      // a counter per part, zero between launches
+    int n_whole;     // tiles computed whole by one workgroup: the first n_whole
+    int n_split;     // tiles split: the last n_split
+    int halves;      // 1 or 2
+    int ways;        // 1 or 3
+    int units() const { return n_split * halves * ways; }
+};
+
+// The split of a d = 128 bf16 launch of W tiles on n_cu CUs (one workgroup
+// per CU), over nkb key blocks: the last round's t = W mod n_cu tiles are
+// shared by more workgroups where that shortens it.  In rounds, of which a
+// whole tile takes 1:
+//   three key segments of halves of 128 queries   0.25, and 4 us to merge
+//   three key segments                            0.33, and 4 us
+//   halves (half the waves only load)             0.65, to 0.85 with every CU busy
+//   three key segments in two rounds              0.67, and 4 us
+// and the first that fits is taken, in this order: 64 tiles of S = 4096 take
+// 92 us whole, 64 in halves, 38 in thirds; 128 tiles 92, 79 and, in thirds
+// over two rounds, 88; 155 tiles of S = 7800 165 and 145.  Segments need
+// scratch (none: halves or whole tiles, the same
+// results).  With sp->tail >= 0, t is that and the last
+// min(tail, W) tiles are split: a launch whose last round is shared with
+// another stream's launch splits the tiles that close the pooled rounds.
+inline TailSplit plan_split(int64_t W, int nkb, int n_cu, const SplitScratch *sp) {
+    TailSplit p{nullptr, nullptr, nullptr, static_cast<int>(W), 0, 1, 1};
+    const int64_t n = n_cu;
+    if (n < 2) return p;
+    const int64_t t = sp && sp->tail >= 0 ? sp->tail : W % n, rem = std::min(t, W);
+    if (rem == 0) return p;
+    auto scratch = [&](int halves) {
+        return sp && sp->part && nkb >= kKeySegmentMinBlocks && rem * halves * kKeySegments <= sp->slots &&
+               rem * halves <= sp->counters;
+    };
+    if (6 * t <= n && scratch(2)) p.halves = 2, p.ways = 3;
+    else if (3 * t <= n && scratch(1)) p.ways = 3;
+    else if (2 * t <= n) p.halves = 2;
+    else if (3 * t <= 2 * n && scratch(1)) p.ways = 3;
+    else return p;
+    if (p.ways > 1) {
+        p.part = static_cast<char *>(sp->part);
+        p.ml = static_cast<char *>(sp->ml);
+        p.count = sp->count;
+    }
+    p.n_whole = static_cast<int>(W - rem);
+    p.n_split = static_cast<int>(rem);
+    return p;
+}
+
+}  // namespace hcms

@@ -1,0 +1,104 @@
+"""Host rules of the attention launch's shared tiles (csrc/split_plan.h),
+compiled on their own: no GPU."""
+import os
+import subprocess
+
+import pytest
+
+from paper_2607_01817_amd import build
+
+DRIVER = r"""
+#include <cstdio>
+#include "split_plan.h"
+using namespace hcms;
+constexpr int64_t kSlot = 68 * 1024;
+// region mem r n_cu            -> part ml count (offsets), slots counters n_cu
+// plan W nkb n_cu mem r tail   -> n_whole n_split halves ways has_scratch
+int main() {
+    char what[16];
+    while (std::scanf("%15s", what) == 1) {
+        long long W, mem, tail;
+        int nkb, n_cu, r;
+        if (what[0] == 'r') {
+            if (std::scanf("%lld %d %d", &mem, &r, &n_cu) != 3) return 1;
+            const SplitScratch s = split_region(reinterpret_cast<void *>(mem), r, n_cu, kSlot);
+            std::printf("%lld %lld %lld %d %d %d\n", (long long)s.part - mem, (long long)s.ml - mem,
+                        (long long)s.count - mem, s.slots, s.counters, s.n_cu);
+        } else {
+            if (std::scanf("%lld %d %d %lld %d %lld", &W, &nkb, &n_cu, &mem, &r, &tail) != 6) return 1;
+            SplitScratch s = split_region(mem < 0 ? nullptr : reinterpret_cast<void *>(mem), r, n_cu, kSlot);
+            s.tail = tail;
+            const TailSplit p = plan_split(W, nkb, n_cu, mem < 0 ? nullptr : &s);
+            std::printf("%d %d %d %d %d\n", p.n_whole, p.n_split, p.halves, p.ways, p.part && p.ml && p.count);
+        }
+    }
+    std::printf("%lld %lld\n", (long long)split_bytes(256, kSlot), (long long)split_counter_bytes(256));
+}
+"""
+MEM = 1 << 40      # an address that nothing reads
+SLOT = 68 * 1024
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    d = tmp_path_factory.mktemp("split")
+    (d / "driver.cpp").write_text(DRIVER)
+    subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-fsanitize=undefined",
+                    "-fno-sanitize-recover=undefined", "-I", build.CSRC, str(d / "driver.cpp"),
+                    "-o", str(d / "driver")], check=True)
+
+    def ask(lines):
+        r = subprocess.run([str(d / "driver")], input="\n".join(lines) + "\n", text=True,
+                           capture_output=True)
+        assert r.returncode == 0, (r.returncode, r.stderr[-500:])
+        return [tuple(map(int, ln.split())) for ln in r.stdout.splitlines()]
+
+    return ask
+
+
+def test_regions_fill_the_scratch_without_overlap(rules):
+    a, b, (total, counters) = rules([f"region {MEM} 0 256", f"region {MEM} 1 256"])
+    spans = []
+    for part, ml, count, slots, n_count, n_cu in (a, b):
+        assert n_cu == 256 and slots == n_count
+        spans += [(part, slots * (SLOT - 4096)), (ml, slots * 4096), (count, n_count * 4)]
+        assert part % 16 == 0 and ml % 16 == 0 and count % 4 == 0
+        assert count >= total - counters    # the zeroed end
+    end = 0
+    for at, n in sorted(spans):
+        assert at == end
+        end = at + n
+    assert end == total
+
+
+@pytest.mark.parametrize("mem", [0, -1])
+def test_launches_without_scratch_split_no_tile_by_segments(rules, mem):
+    """A context whose scratch could not be had (an empty region), and a call
+    without one: whole tiles or halves, whatever the size."""
+    if mem == 0:
+        part, ml, count, slots, n_count, n_cu = rules(["region 0 0 256"])[0]
+        assert (slots, n_count, n_cu) == (0, 0, 256)
+    asked = [(W, nkb, n) for n in (1, 2, 3, 80, 256) for W in (1, 2, 40, 100, 128, 129, 155, 256, 1100)
+             for nkb in (1, 12, 900)]
+    got = rules([f"plan {W} {nkb} {n} {mem} 0 -1" for W, nkb, n in asked])
+    for (W, nkb, n), (whole, split, halves, ways, scratch) in zip(asked, got):
+        t = W % n
+        assert whole + split == W and ways == 1 and scratch == 0
+        assert (split, halves) == ((t, 2) if n >= 2 and 0 < 2 * t <= n else (0, 1))
+
+
+def test_an_unset_scratch_splits_nothing(rules):
+    """Zero compute units in the scratch (a region that was never filled in)."""
+    assert rules([f"plan {W} 900 0 0 0 -1" for W in (1, 155, 1100)])[:3] == \
+        [(W, 0, 1, 1, 0) for W in (1, 155, 1100)]
+
+
+@pytest.mark.parametrize("r", [0, 1])
+def test_split_units_fit_the_scratch(rules, r):
+    slots = 512 if r == 0 else 256
+    asked = [(W, nkb, tail) for W in range(1, 520) for nkb in (11, 12) for tail in (-1, 0, 40, 76, 170)]
+    got = rules([f"plan {W} {nkb} 256 {MEM} {r} {tail}" for W, nkb, tail in asked])
+    for (W, nkb, tail), (whole, split, halves, ways, scratch) in zip(asked, got):
+        assert whole + split == W and halves in (1, 2) and ways in (1, 3)
+        assert split in (0, min(W % 256 if tail < 0 else tail, W))
+        assert scratch == (ways == 3) and (ways == 1 or (nkb >= 12 and split * halves * ways <= slots))
