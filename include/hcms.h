@@ -14,7 +14,7 @@
  * Conventions for every entry point
  *   - Buffers are device memory owned by the caller, contiguous, row-major,
  *     16-byte aligned.  The library allocates no device memory on any call
- *     except hcms_ctx_create (events, and 51 MiB to share tiles in).
+ *     except hcms_ctx_create (events, and 68 MiB to share tiles in).
  *   - `stream` arguments are hipStream_t handles passed as void*.  NULL is the
  *     null stream of the current device.  Streams are borrowed, never destroyed.
  *   - All compute calls are asynchronous and stream-ordered; a kernel fault
@@ -425,8 +425,13 @@ typedef struct hcms_ctx hcms_ctx;
  * Create a scheduler context bound to HIP device `device`: it owns the events
  * of up to `max_chunks` chunks (created once, reused by every call; the
  * device-level stream/event caching of Sec. 4.1), so hcms_forward creates
- * nothing.  Errors: NULL, ARG (device out of range), CHUNKS (max_chunks < 1),
- * HIP.
+ * nothing.  It also owns the memory in which d = 128 bf16 launches share
+ * tiles, three regions that each serve one stream at a time: a context may be
+ * used from several main streams, by one thread at a time, and a launch that
+ * finds no region free shares tiles without one (the same results).  Replays
+ * of a captured graph are not seen by the context: they must not overlap other
+ * work of the context that was issued or captured on the captured streams.
+ * Errors: NULL, ARG (device out of range), CHUNKS (max_chunks < 1), HIP.
  */
 HCMS_API int hcms_ctx_create(int device, int max_chunks, hcms_ctx **out);
 
@@ -446,8 +451,8 @@ HCMS_API int hcms_ctx_num_cu(const hcms_ctx *ctx);
    Errors: NULL (ctx), ARG (bytes < 0), ALIGN. */
 HCMS_API int hcms_ctx_set_ds_workspace(hcms_ctx *ctx, void *ws, int64_t bytes);
 
-/* Destroy a context (its events).  The caller must not destroy it while work
-   that waits on its events is still pending.  NULL is accepted. */
+/* Destroy a context (its events and memory).  The caller must not destroy it
+   while work that uses them is still pending.  NULL is accepted. */
 HCMS_API int hcms_ctx_destroy(hcms_ctx *ctx);
 
 /*

@@ -458,12 +458,13 @@ struct hcms_ctx {
     std::vector<hipEvent_t> t_begin;     // [call][kind][chunk] timing events
     std::vector<hipEvent_t> t_end;
     std::vector<int> timed_chunks;       // chunk count of each timed call
-    // Scratch that lets an attention launch split its last round of tiles:
-    // one region for launches on the main stream, one for the compute stream
-    // (launches on one stream are ordered, so each region serves one launch
-    // at a time).  Empty regions: no tile split by segments, the same results.
+    // Scratch that lets an attention launch split its last round of tiles, in
+    // regions that each serve one stream at a time (SplitPool).  Empty
+    // regions: no tile split by segments, the same results.
     void *split_mem = nullptr;
-    hcms::SplitScratch split[2] = {};
+    hcms::SplitScratch split[hcms::kSplitRegions] = {};
+    hipEvent_t split_event[hcms::kSplitRegions] = {};
+    hcms::SplitPool pool;
     // Caller-owned score-gradient workspace of hcms_backward: two regions of
     // ds_region bytes, one for backward launches on the main stream, one for
     // those on the compute stream (NULL: none).
@@ -703,6 +704,53 @@ auto copy_lds_reserve(int mode, int C) {
     };
 }
 
+// The split scratch of one attention launch of W tiles on stream s (role 0:
+// the main stream, 1: the compute stream), taken before it and released by
+// done() after it.
+class SplitUse {
+public:
+    SplitUse(hcms_ctx *ctx, hipStream_t s, int role, int S, int d, int dtype, int64_t W, int64_t tail)
+        : ctx_(ctx), s_(s) {
+        none_.n_cu = ctx->n_cu;
+        none_.tail = tail;
+        hcms::SplitScratch most = ctx->split[0];
+        most.tail = tail;
+        if (!hcms::attention_splits_by_segments(W, S, d, dtype, &most)) return;
+        hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+        if (s && hipStreamIsCapturing(s, &status) != hipSuccess) {
+            (void)hipGetLastError();
+            status = hipStreamCaptureStatusActive;
+        }
+        capturing_ = status != hipStreamCaptureStatusNone;
+        bool wait = false;
+        const int r = ctx->pool.find(s, role, capturing_, &wait);
+        if (r < 0) return;
+        if (wait && hipStreamWaitEvent(s, ctx->split_event[r], 0) != hipSuccess) {
+            (void)hipGetLastError();
+            return;
+        }
+        ctx->pool.own(r, s);
+        r_ = r;
+        mine_ = ctx->split[r];
+        mine_.tail = tail;
+    }
+    const hcms::SplitScratch *scratch() const { return r_ < 0 ? &none_ : &mine_; }
+    // The launch's status e, after what the region's next user needs.
+    hipError_t done(hipError_t e) {
+        if (r_ < 0 || !ctx_->pool.records(r_, capturing_) || e != hipSuccess) return e;
+        if (hipEventRecord(ctx_->split_event[r_], s_) == hipSuccess) ctx_->pool.recorded(r_);
+        else (void)hipGetLastError();
+        return e;
+    }
+
+private:
+    hcms_ctx *ctx_;
+    hipStream_t s_;
+    int r_ = -1;
+    bool capturing_ = false;
+    hcms::SplitScratch none_{}, mine_{};
+};
+
 // Issues a validated hcms_forward (S > 0) in the resolved mode.
 int issue_forward(const ForwardArgs &args, int mode, int log2u) {
     ForwardArgs f = args;
@@ -720,26 +768,22 @@ int issue_forward(const ForwardArgs &args, int mode, int log2u) {
         return static_cast<char *>(p) + head_bytes * first;
     };
     const auto beside = copy_lds_reserve(mode, f.n_chunks);
-    // The split scratch of the stream an attention launch runs on.  In the
-    // lanes plan the two lanes' launches share rounds, so none splits its own
-    // last round.  The last launch of each lane (chunks C - 2 and C - 1), whose
-    // tiles close the pooled rounds, splits its last rem tiles instead, rem
-    // the tiles past the last whole pooled round (the chunks' workgroups
-    // summed, mod n_cu): which lane's tiles end the pooled rounds depends on
-    // how the two queues' workgroups interleave, so both split.
+    // The tiles a launch splits.  In the lanes plan the two lanes' launches
+    // share rounds, so none splits its own last round.  The last launch of
+    // each lane (chunks C - 2 and C - 1), whose tiles close the pooled rounds,
+    // splits its last rem tiles instead, rem the tiles past the last whole
+    // pooled round (the chunks' workgroups summed, mod n_cu): which lane's
+    // tiles end the pooled rounds depends on how the two queues' workgroups
+    // interleave, so both split.
     const int64_t tiles = (static_cast<int64_t>(f.S) + hcms::attention_queries_per_block(f.d) - 1) /
                           hcms::attention_queries_per_block(f.d);
     int64_t pooled = 0;
     for (int c = 0; c < f.n_chunks; ++c) pooled += tiles * f.chunk_sizes[c];
-    hcms::SplitScratch lanes_tail{};
-    auto split_for = [&](hipStream_t s, int c) -> const hcms::SplitScratch * {
-        const int r = s == static_cast<hipStream_t>(f.main_stream) ? 0
-                      : s == static_cast<hipStream_t>(f.compute_stream) ? 1 : -1;
-        if (r < 0) return nullptr;
-        if (mode != HCMS_MODE_LANES || f.n_chunks < 2) return &f.ctx->split[r];
-        lanes_tail = f.ctx->split[r];
-        lanes_tail.tail = c < f.n_chunks - 2 ? 0 : pooled % f.ctx->n_cu;
-        return &lanes_tail;
+    auto split_of = [&](hipStream_t s, int c, int hc) {
+        const bool lanes = mode == HCMS_MODE_LANES && f.n_chunks >= 2;
+        const int64_t tail = !lanes ? -1 : c < f.n_chunks - 2 ? 0 : pooled % f.ctx->n_cu;
+        return SplitUse(f.ctx, s, s == static_cast<hipStream_t>(f.main_stream) ? 0 : 1, f.S, f.d, f.dtype,
+                        tiles * hc, tail);
     };
     auto launch = [&](int kind, int c, int h0, int hc, hipStream_t s) -> hipError_t {
         if (kind == HCMS_OP_PACK) {
@@ -747,11 +791,13 @@ int issue_forward(const ForwardArgs &args, int mode, int log2u) {
             void *dst[3] = {at(f.q_hm, c, h0), at(f.k_hm, c, h0), at(f.v_hm, c, h0)};
             return hcms::launch_pack(src, dst, 3, f.S, f.H, h0, hc, log2u, beside(kind, c), s);
         }
-        if (kind == HCMS_OP_ATTENTION)
-            return hcms::launch_attention(at(f.q_hm, c, h0), at(f.k_hm, c, h0), at(f.v_hm, c, h0),
-                                          at(f.o_hm, c, h0),
-                                          f.lse ? f.lse + static_cast<int64_t>(h0) * f.S : nullptr,
-                                          f.S, hc, f.d, c_log2e, f.dtype, split_for(s, c), s);
+        if (kind == HCMS_OP_ATTENTION) {
+            SplitUse split = split_of(s, c, hc);
+            return split.done(hcms::launch_attention(
+                at(f.q_hm, c, h0), at(f.k_hm, c, h0), at(f.v_hm, c, h0), at(f.o_hm, c, h0),
+                f.lse ? f.lse + static_cast<int64_t>(h0) * f.S : nullptr, f.S, hc, f.d, c_log2e,
+                f.dtype, split.scratch(), s));
+        }
         const void *src[1] = {at(f.o_hm, c, h0)};
         void *dst[1] = {f.o_seq};
         return hcms::launch_unpack(src, dst, 1, f.S, f.H, h0, hc, log2u, beside(kind, c), s);
@@ -781,10 +827,11 @@ int issue_forward(const ForwardArgs &args, int mode, int log2u) {
                 cp[r].dst[0] = f.o_seq;
             }
         }
-        return hcms::launch_attention_riding(
+        SplitUse split = split_of(s, c, hc);
+        return split.done(hcms::launch_attention_riding(
             at(f.q_hm, c, h0), at(f.k_hm, c, h0), at(f.v_hm, c, h0), at(f.o_hm, c, h0),
             f.lse ? f.lse + static_cast<int64_t>(h0) * f.S : nullptr, f.S, hc, f.d, c_log2e,
-            f.dtype, cp, n, f.H, f.ctx->n_cu, split_for(s, c), riding, s);
+            f.dtype, cp, n, f.H, f.ctx->n_cu, split.scratch(), riding, s));
     };
     return execute_plan(f.ctx, mode, f.chunk_sizes, f.n_chunks, f.main_stream, f.copy_stream,
                         f.compute_stream, launch, ride);
@@ -1225,8 +1272,15 @@ int hcms_ctx_create(int device, int max_chunks, hcms_ctx **out) {
         }
         ctx->events.push_back(ev);
     }
-    // Split scratch: a region for launches on the main stream and one for
-    // those on the compute stream.  If it cannot be had, the regions are empty.
+    for (hipEvent_t &ev : ctx->split_event) {
+        e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
+        if (e != hipSuccess) {
+            ev = nullptr;
+            hcms_ctx_destroy(ctx);
+            return hip_fail(e, "hipEventCreateWithFlags");
+        }
+    }
+    // Split scratch.  If it cannot be had, the regions are empty.
     {
         const int64_t slot = hcms::attention_split_slot_bytes();
         const int64_t bytes = hcms::split_bytes(ctx->n_cu, slot), zero = hcms::split_counter_bytes(ctx->n_cu);
@@ -1238,7 +1292,8 @@ int hcms_ctx_create(int device, int max_chunks, hcms_ctx **out) {
         }
         (void)hipGetLastError();
         ctx->split_mem = mem;
-        for (int r = 0; r < 2; ++r) ctx->split[r] = hcms::split_region(mem, r, ctx->n_cu, slot);
+        for (int r = 0; r < hcms::kSplitRegions; ++r)
+            ctx->split[r] = hcms::split_region(mem, r, ctx->n_cu, slot);
     }
     *out = ctx;
     return ok();
@@ -1250,6 +1305,8 @@ int hcms_ctx_destroy(hcms_ctx *ctx) {
     for (hipEvent_t ev : ctx->events) (void)hipEventDestroy(ev);
     for (hipEvent_t ev : ctx->t_begin) (void)hipEventDestroy(ev);
     for (hipEvent_t ev : ctx->t_end) (void)hipEventDestroy(ev);
+    for (hipEvent_t ev : ctx->split_event)
+        if (ev) (void)hipEventDestroy(ev);
     if (ctx->split_mem) (void)hipFree(ctx->split_mem);
     delete ctx;
     return ok();

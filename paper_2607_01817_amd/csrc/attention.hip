@@ -1295,6 +1295,11 @@ int attention_blocks_per_cu(int d) { return d == 128 ? Shape<128>::PER_CU : Shap
 
 int64_t attention_split_slot_bytes() { return dma::kStashB + 256 * int64_t{sizeof(float4)}; }   // ml: 4 KiB
 
+bool attention_splits_by_segments(int64_t W, int S, int d, int dtype, const SplitScratch *split) {
+    return kLdsDma && d == dma::kD && dtype == 0 &&
+           plan_split(W, (S + kBC - 1) / kBC, split->n_cu, split).ways > 1;
+}
+
 int attention_split_ways(int64_t W, int S, int d, int dtype, int n_cu) {
     if (!(kLdsDma && d == dma::kD && dtype == 0)) return 1;
     const int64_t rem = W % n_cu;

@@ -51,6 +51,8 @@ int attention_blocks_per_cu(int d);
 
 // Bytes of a partial state of SplitScratch (split_plan.h).
 int64_t attention_split_slot_bytes();
+// Whether a launch of W tiles splits some of them by segments in this scratch.
+bool attention_splits_by_segments(int64_t W, int S, int d, int dtype, const SplitScratch *split);
 // Workgroups per split tile of the time model and of the mode rule, for a
 // launch of W tiles on n_cu CUs: 3 or 2 where the last round's W mod n_cu
 // tiles, shared by so many workgroups each, fit in one round, else 1.  (The

@@ -31,10 +31,16 @@ struct SplitScratch {
     int64_t tail = -1;
 };
 
-// The scratch of launches on the main stream (r = 0: 2 n_cu slots) and on the
-// compute stream (r = 1: n_cu), as many counters each.
+// A context's scratch: region 0 of 2 n_cu slots and regions 1 and 2 of n_cu,
+// as many counters each.
+inline constexpr int kSplitRegions = 3;
 inline int split_slots(int r, int n_cu) { return r == 0 ? 2 * n_cu : n_cu; }
-inline int64_t split_slots_all(int n_cu) { return int64_t{split_slots(0, n_cu)} + split_slots(1, n_cu); }
+inline int64_t split_slots_before(int r, int n_cu) {
+    int64_t n = 0;
+    for (int i = 0; i < r; ++i) n += split_slots(i, n_cu);
+    return n;
+}
+inline int64_t split_slots_all(int n_cu) { return split_slots_before(kSplitRegions, n_cu); }
 // Bytes of all of it with states of slot_bytes (4 KiB of them for ml), and
 // their part that has to start at zero: the counters, at the end.
 inline int64_t split_bytes(int n_cu, int64_t slot_bytes) { return split_slots_all(n_cu) * (slot_bytes + 4); }
@@ -46,13 +52,64 @@ inline SplitScratch split_region(void *mem, int r, int n_cu, int64_t slot_bytes)
     s.n_cu = n_cu;
     if (!mem) return s;
     char *const base = static_cast<char *>(mem);
-    const int64_t first = r == 0 ? 0 : split_slots(0, n_cu);
+    const int64_t first = split_slots_before(r, n_cu);
     s.slots = s.counters = split_slots(r, n_cu);
     s.part = base + first * slot_bytes;
     s.ml = base + first * slot_bytes + s.slots * (slot_bytes - 4096);
     s.count = reinterpret_cast<int *>(base + split_slots_all(n_cu) * slot_bytes + first * 4);
     return s;
 }
+
+// Which stream a region belongs to.  Two launches may be in one region only
+// one after the other, so a region serves the launches of one stream, and
+// moves to another stream behind an event recorded after its last use.  A
+// context used on one main and one compute stream, the ordinary one, records
+// none: its streams take regions 0 and 1.  Events begin with the first launch
+// that finds its region taken; that one takes region 2.  A region used in a
+// capture stays with its stream, since its launches are replayed whenever the
+// program likes, and a launch in a capture waits for no event from outside.
+// A launch that gets no region splits no tile by segments.
+class SplitPool {
+public:
+    // The region for a launch on `stream`, -1: none.  role: 0 for the main
+    // stream, 1 for the compute stream.  *wait: the launch's stream has to
+    // wait for the region's event first.  own() then makes it the stream's.
+    int find(const void *stream, int role, bool capturing, bool *wait) {
+        *wait = false;
+        for (int r = 0; r < kSplitRegions; ++r)
+            if (at_[r].owned && at_[r].stream == stream) return r;
+        const int order[2] = {role, 2};
+        for (int r : order)
+            if (!at_[r].owned) {
+                shared_ = shared_ || r != role;
+                return r;
+            }
+        shared_ = true;
+        for (int r : order)
+            if (at_[r].recorded && !capturing) {
+                *wait = true;
+                return r;
+            }
+        return -1;
+    }
+    void own(int r, const void *stream) { at_[r].owned = true, at_[r].stream = stream; }
+    // After a launch in region r: whether to record its event behind it, and
+    // that this was done (or failed).
+    bool records(int r, bool capturing) {
+        at_[r].captured = at_[r].captured || capturing;
+        at_[r].recorded = false;
+        return shared_ && !at_[r].captured;
+    }
+    void recorded(int r) { at_[r].recorded = true; }
+
+private:
+    struct Use {
+        const void *stream = nullptr;
+        bool owned = false, recorded = false, captured = false;
+    };
+    Use at_[kSplitRegions];
+    bool shared_ = false;   // some launch found its region taken
+};
 
 // Tiles shared by several workgroups (the launch's last, partial round of
 // tiles; see plan_split).  Of the `units` = n_split * halves * ways workgroups

@@ -1,6 +1,6 @@
 """Host rules of the attention launch's shared tiles (csrc/split_plan.h),
 compiled on their own: no GPU."""
-import os
+import random
 import subprocess
 
 import pytest
@@ -14,8 +14,10 @@ using namespace hcms;
 constexpr int64_t kSlot = 68 * 1024;
 // region mem r n_cu            -> part ml count (offsets), slots counters n_cu
 // plan W nkb n_cu mem r tail   -> n_whole n_split halves ways has_scratch
+// use stream role capturing    -> region wait record, a launch of one pool
 int main() {
     char what[16];
+    SplitPool pool;
     while (std::scanf("%15s", what) == 1) {
         long long W, mem, tail;
         int nkb, n_cu, r;
@@ -24,6 +26,18 @@ int main() {
             const SplitScratch s = split_region(reinterpret_cast<void *>(mem), r, n_cu, kSlot);
             std::printf("%lld %lld %lld %d %d %d\n", (long long)s.part - mem, (long long)s.ml - mem,
                         (long long)s.count - mem, s.slots, s.counters, s.n_cu);
+        } else if (what[0] == 'u') {
+            int role, capturing;
+            if (std::scanf("%lld %d %d", &mem, &role, &capturing) != 3) return 1;
+            const void *stream = reinterpret_cast<void *>(mem);
+            bool wait = false, record = false;
+            const int at = pool.find(stream, role, capturing, &wait);
+            if (at >= 0) {
+                pool.own(at, stream);
+                record = pool.records(at, capturing);
+                if (record) pool.recorded(at);
+            }
+            std::printf("%d %d %d\n", at, wait, record);
         } else {
             if (std::scanf("%lld %d %d %lld %d %lld", &W, &nkb, &n_cu, &mem, &r, &tail) != 6) return 1;
             SplitScratch s = split_region(mem < 0 ? nullptr : reinterpret_cast<void *>(mem), r, n_cu, kSlot);
@@ -57,9 +71,9 @@ def rules(tmp_path_factory):
 
 
 def test_regions_fill_the_scratch_without_overlap(rules):
-    a, b, (total, counters) = rules([f"region {MEM} 0 256", f"region {MEM} 1 256"])
+    *regions, (total, counters) = rules([f"region {MEM} {r} 256" for r in range(3)])
     spans = []
-    for part, ml, count, slots, n_count, n_cu in (a, b):
+    for part, ml, count, slots, n_count, n_cu in regions:
         assert n_cu == 256 and slots == n_count
         spans += [(part, slots * (SLOT - 4096)), (ml, slots * 4096), (count, n_count * 4)]
         assert part % 16 == 0 and ml % 16 == 0 and count % 4 == 0
@@ -93,7 +107,7 @@ def test_an_unset_scratch_splits_nothing(rules):
         [(W, 0, 1, 1, 0) for W in (1, 155, 1100)]
 
 
-@pytest.mark.parametrize("r", [0, 1])
+@pytest.mark.parametrize("r", [0, 1, 2])
 def test_split_units_fit_the_scratch(rules, r):
     slots = 512 if r == 0 else 256
     asked = [(W, nkb, tail) for W in range(1, 520) for nkb in (11, 12) for tail in (-1, 0, 40, 76, 170)]
@@ -102,3 +116,43 @@ def test_split_units_fit_the_scratch(rules, r):
         assert whole + split == W and halves in (1, 2) and ways in (1, 3)
         assert split in (0, min(W % 256 if tail < 0 else tail, W))
         assert scratch == (ways == 3) and (ways == 1 or (nkb >= 12 and split * halves * ways <= slots))
+
+
+def _uses(rules, uses):
+    return rules([f"use {stream} {role} {capturing}" for stream, role, capturing in uses])[:len(uses)]
+
+
+def test_one_main_and_one_compute_stream_record_no_event(rules):
+    got = _uses(rules, [(7, 0, 0), (8, 1, 0)] * 3)
+    assert got == [(0, 0, 0), (1, 0, 0)] * 3
+
+
+def test_a_capture_on_another_stream_keeps_a_region_of_its_own(rules):
+    """Warmed up on stream 7, captured on stream 9, then used on 7 again and on
+    11: 9's region is never handed on, and no capture waits for an event."""
+    got = _uses(rules, [(7, 0, 0), (9, 0, 1), (7, 0, 0), (11, 0, 0), (12, 0, 1)])
+    assert got == [(0, 0, 0), (2, 0, 0), (0, 0, 1), (0, 1, 1), (-1, 0, 0)]
+
+
+@pytest.mark.parametrize("seed", range(20))
+def test_a_region_changes_streams_only_behind_an_event(rules, seed):
+    """Random streams, roles and captures: where a region's launch follows one
+    of another stream, it waits for an event recorded behind that launch, and
+    neither of the two is in a capture."""
+    rng = random.Random(seed)
+    streams = [0] + rng.sample(range(1, 100), rng.randint(1, 5))
+    uses = [(rng.choice(streams), rng.randint(0, 1), int(seed % 2 and rng.random() < 0.1))
+            for _ in range(200)]
+    last, handed = {}, 0
+    for (stream, role, capturing), (r, wait, record) in zip(uses, _uses(rules, uses)):
+        if r < 0:
+            continue
+        if r in last and last[r][0] != stream:
+            handed += 1
+            assert wait and last[r][1] and not capturing and not last[r][2]
+        else:
+            assert not wait
+        captured = capturing or (r in last and last[r][0] == stream and last[r][2])
+        assert not (record and capturing)
+        last[r] = (stream, record, captured)
+    assert handed > 0 or seed % 2 or len(streams) <= 3
