@@ -314,7 +314,8 @@ typedef struct hcms_op {
 HCMS_API int hcms_plan(int n_chunks, int mode, hcms_op *ops, int cap);
 
 /*
- * The plan HCMS_MODE_AUTO runs: attention of chunk c launches
+ * The plan HCMS_MODE_AUTO runs where hcms_forward does not join the chunks
+ * into one (the serial plan then): attention of chunk c launches
  * W_c = ceil(S / Br) * H_c workgroups, of which n_cu * B run at once (Br and
  * B the attention tiling for head dimension d: 256 queries and one workgroup
  * per CU for d = 128, 128 and two for d = 64).  One lane takes
@@ -435,8 +436,9 @@ typedef struct hcms_ctx hcms_ctx;
  */
 HCMS_API int hcms_ctx_create(int device, int max_chunks, hcms_ctx **out);
 
-/* The plan mode the context's last hcms_forward ran (HCMS_MODE_AUTO resolved;
-   -1 before the first call), and the device's compute-unit count. */
+/* The plan mode the context's last forward or backward ran (HCMS_MODE_AUTO
+   resolved, HCMS_MODE_SERIAL where it joined the chunks; -1 before the first
+   call), and the device's compute-unit count. */
 HCMS_API int hcms_ctx_last_mode(const hcms_ctx *ctx);
 HCMS_API int hcms_ctx_num_cu(const hcms_ctx *ctx);
 

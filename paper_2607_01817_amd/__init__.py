@@ -187,7 +187,8 @@ def plan(n_chunks: int, mode: int = MODE_PIPELINED) -> list[tuple[int, int, int,
 
 
 def auto_mode(S: int, d: int, chunk_sizes, n_cu: int, dtype: int = BF16) -> int:
-    """The plan mode MODE_AUTO runs for these chunks on n_cu compute units."""
+    """The plan mode MODE_AUTO runs for these chunks on n_cu compute units
+    (MODE_SERIAL where a forward or backward joins them into one)."""
     sizes, n = _ints(chunk_sizes)
     return _check(load().hcms_auto_mode(S, d, dtype, sizes, n, n_cu))
 
@@ -502,7 +503,8 @@ class Context:
 
     @property
     def last_mode(self) -> int:
-        """Plan mode of the last forward (MODE_AUTO resolved), -1 before any."""
+        """Plan mode of the last forward or backward (MODE_AUTO resolved;
+        MODE_SERIAL where it joined the chunks), -1 before any."""
         return load().hcms_ctx_last_mode(self._h)
 
     def close(self):

@@ -451,7 +451,7 @@ struct hcms_ctx {
     int device = 0;
     int max_chunks = 0;
     int n_cu = 0;                        // compute units of the device
-    int last_mode = -1;                  // plan mode of the last hcms_forward
+    int last_mode = -1;                  // plan mode of the last forward or backward
     std::vector<hipEvent_t> events;      // 2 * max_chunks + 2 sync events
     std::vector<hcms_op> plan;           // scratch for the op list
     int timing_calls = 0;                // calls to time (0 = off)
@@ -755,8 +755,9 @@ private:
 int issue_forward(const ForwardArgs &args, int mode, int log2u) {
     ForwardArgs f = args;
     if (f.mode == HCMS_MODE_AUTO && f.slot_heads == 0 && joins_chunks(f.ctx, f.S, f.H, f.d)) {
-        f.chunk_sizes = &f.H;   // every plan of one chunk is the serial plan
+        f.chunk_sizes = &f.H;
         f.n_chunks = 1;
+        mode = HCMS_MODE_SERIAL;   // as every plan of one chunk
     }
     const int64_t head_bytes = static_cast<int64_t>(f.S) * f.d * elem_bytes(f.dtype);
     const float c_log2e = scale_log2e(f.scale);
@@ -1532,6 +1533,7 @@ int hcms_backward(hcms_ctx *ctx, const void *dout_seq, void *dq_seq, void *dk_se
         (!ds_path || ctx->ds_region >= ds_head * H)) {
         chunk_sizes = &H;
         n_chunks = 1;
+        mode = HCMS_MODE_SERIAL;
     }
 
     const int64_t head_bytes = static_cast<int64_t>(S) * d * elem_bytes(dtype);

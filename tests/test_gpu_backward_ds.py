@@ -188,3 +188,32 @@ def test_ds_pipeline_bitwise_across_modes_and_chunkings(hcms, name):
                 assert ctx.last_mode == hcms.MODE_LANES, (name, sizes, ctx.last_mode)
     ctx.set_ds_workspace(None)
     ctx.close()
+
+
+@pytest.mark.parametrize("S,H,sizes", [(1100, 6, (3, 3)), (3001, 8, (4, 4)), (513, 5, (2, 2, 1))])
+def test_joined_chunks_with_ds_equal_the_plans_of_the_chunks(hcms, S, H, sizes):
+    """Chunks that fill at most one round run joined where a region of the
+    workspace holds every head, in lanes where it does not: the same bits as
+    the direct backward and the explicit plans."""
+    log(f"[backward ds joined] S={S} H={H} chunks={sizes}")
+    g = torch.Generator().manual_seed(S + H)
+    q, k, v, do = (torch.randn(S, H, 128, generator=g).to(torch.bfloat16).cuda() for _ in range(4))
+    scale = 128 ** -0.5
+    hm = [x.permute(1, 0, 2).contiguous() for x in (q, k, v, do)]
+    out, lse = hcms.attention_lse(hm[0], hm[1], hm[2], scale)
+    ref = [t.permute(1, 0, 2).contiguous()
+           for t in hcms.attention_backward(hm[0], hm[1], hm[2], out, hm[3], lse, scale, ds=_ws(hcms, S, 1))]
+    for heads, want in ((H, hcms.MODE_SERIAL), (H - 1, hcms.MODE_LANES)):
+        ctx = hcms.Context()
+        ctx.set_ds_workspace(_ws(hcms, S, 2 * heads))
+        for mode in (hcms.MODE_AUTO, hcms.MODE_SERIAL, hcms.MODE_LANES):
+            ws = [torch.empty_like(hm[0]) for _ in range(4)]
+            lse2 = torch.empty_like(lse)
+            ctx.forward(q, k, v, 1, scale, sizes, mode=mode, workspaces=ws, lse=lse2)
+            got = ctx.backward(do, 1, scale, sizes, ws, lse2, mode=mode)
+            if mode == hcms.MODE_AUTO:
+                assert ctx.last_mode == want, heads
+            for a, b, nm in zip(got, ref, ("dq", "dk", "dv")):
+                assert torch.equal(bits(a), bits(b)), (heads, mode, nm)
+        torch.cuda.synchronize()
+        ctx.close()

@@ -320,8 +320,17 @@ def test_auto_mode_runs_the_predicted_plan(hcms, name, sizes):
     ctx = hcms.Context()
     assert ctx.num_cu == torch.cuda.get_device_properties(0).multi_processor_count
     assert ctx.last_mode == -1
+    predicted = hcms.auto_mode(w.S, w.d, sizes, ctx.num_cu)
     ctx.forward(q, k, v, w.P, w.scale, sizes, mode=hcms.MODE_AUTO)
-    assert ctx.last_mode == hcms.auto_mode(w.S, w.d, sizes, ctx.num_cu)
+    # Chunks that together fill at most one round run joined: one launch of
+    # each kernel, the serial plan.
+    joined = -(-w.S // 256) * w.H <= ctx.num_cu
+    assert ctx.last_mode == (hcms.MODE_SERIAL if joined else predicted)
+    # Timed calls report chunk by chunk and run the predicted plan.
+    ctx.set_timing(1)
+    ctx.forward(q, k, v, w.P, w.scale, sizes, mode=hcms.MODE_AUTO)
+    assert ctx.last_mode == predicted
+    assert len(ctx.kernel_ms(hcms.OP_ATTENTION)) == len(sizes)
     ctx.forward(q, k, v, w.P, w.scale, sizes, mode=hcms.MODE_PIPELINED)
     assert ctx.last_mode == hcms.MODE_PIPELINED
     torch.cuda.synchronize()
