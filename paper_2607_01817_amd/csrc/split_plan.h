@@ -134,17 +134,19 @@ struct TailSplit {
 
 // The split of a d = 128 bf16 launch of W tiles on n_cu CUs (one workgroup
 // per CU), over nkb key blocks: the last round's t = W mod n_cu tiles are
-// shared by more workgroups where that shortens it.  In rounds, of which a
-// whole tile takes 1:
-//   three key segments of halves of 128 queries   0.25, and 4 us to merge
-//   three key segments                            0.33, and 4 us
-//   halves (half the waves only load)             0.65, to 0.85 with every CU busy
-//   three key segments in two rounds              0.67, and 4 us
-// and the first that fits is taken, in this order: 64 tiles of S = 4096 take
-// 92 us whole, 64 in halves, 38 in thirds; 128 tiles 92, 79 and, in thirds
-// over two rounds, 88; 155 tiles of S = 7800 165 and 145.  Segments need
-// scratch (none: halves or whole tiles, the same
-// results).  With sp->tail >= 0, t is that and the last
+// shared by more workgroups where that shortens it, in the first of these ways
+// that fits (times of launches of t tiles at S = 4096, which take 92 us whole
+// with 32 tiles and 97 with 128):
+//   three key segments of halves of 128 queries   32 us with 32 tiles
+//   three key segments                            49 with 64, 53 with 80
+//   halves (half the waves only load)             69 with 96, 77 with 128
+//   three key segments in two rounds              90 with 144 and 94 with 160
+// Segments need scratch (none: halves or whole tiles, the same results).  The
+// last way pays the merge, some 4 us, twice, and gains a tenth of a round:
+// with 160 tiles 70 us against 71 whole at S = 2560 and 64 against 61 at 2048,
+// with 168 tiles 127 against 135 at S = 6000, 89 against 88 at 3584 and 57
+// against 51 at 1536, so it is taken from 40 key blocks on, from 64 with more
+// than 5/8 of a round.  With sp->tail >= 0, t is that and the last
 // min(tail, W) tiles are split: a launch whose last round is shared with
 // another stream's launch splits the tiles that close the pooled rounds.
 inline TailSplit plan_split(int64_t W, int nkb, int n_cu, const SplitScratch *sp) {
@@ -160,7 +162,7 @@ inline TailSplit plan_split(int64_t W, int nkb, int n_cu, const SplitScratch *sp
     if (6 * t <= n && scratch(2)) p.halves = 2, p.ways = 3;
     else if (3 * t <= n && scratch(1)) p.ways = 3;
     else if (2 * t <= n) p.halves = 2;
-    else if (3 * t <= 2 * n && scratch(1)) p.ways = 3;
+    else if (3 * t <= 2 * n && nkb >= (8 * t <= 5 * n ? 40 : 64) && scratch(1)) p.ways = 3;
     else return p;
     if (p.ways > 1) {
         p.part = static_cast<char *>(sp->part);

@@ -118,6 +118,16 @@ def test_split_units_fit_the_scratch(rules, r):
         assert scratch == (ways == 3) and (ways == 1 or (nkb >= 12 and split * halves * ways <= slots))
 
 
+def test_two_rounds_of_segments_only_where_they_are_shorter(rules):
+    """More than half a round of tiles: segments over two rounds from 40 key
+    blocks on, from 64 with more than 160 of 256 tiles, and not beyond 170."""
+    asked = [(t, nkb) for t in (129, 160, 161, 170, 171) for nkb in (12, 39, 40, 63, 64, 900)]
+    got = rules([f"plan {256 + t} {nkb} 256 {MEM} 0 -1" for t, nkb in asked])
+    for (t, nkb), (whole, split, halves, ways, _) in zip(asked, got):
+        shared = t <= 170 and nkb >= (40 if t <= 160 else 64)
+        assert (whole, split, halves, ways) == ((256, t, 1, 3) if shared else (256 + t, 0, 1, 1)), (t, nkb)
+
+
 def _uses(rules, uses):
     return rules([f"use {stream} {role} {capturing}" for stream, role, capturing in uses])[:len(uses)]
 
