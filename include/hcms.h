@@ -303,7 +303,8 @@ typedef struct hcms_op {
  * after every main-stream op before that attention and before every one
  * after it, and overlaps the attention itself (it touches other heads'
  * buffers).  Where a launch cannot carry them (not d = 128 bf16, or its last
- * round leaves fewer than n_cu / 8 CUs idle) hcms_forward runs them right
+ * round leaves fewer than n_cu / 8 CUs idle), or where both are
+ * expected to end earlier one after the other, hcms_forward runs them right
  * after that attention on the main stream instead.
  * With one chunk the inline, lanes and fused plans are the serial plan.
  *   ops : host array of `cap` entries, or NULL to query the count.

@@ -715,7 +715,7 @@ public:
         none_.tail = tail;
         hcms::SplitScratch most = ctx->split[0];
         most.tail = tail;
-        if (!hcms::attention_splits_by_segments(W, S, d, dtype, &most)) return;
+        if (!hcms::attention_may_split_by_segments(W, S, d, dtype, &most)) return;
         hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
         if (s && hipStreamIsCapturing(s, &status) != hipSuccess) {
             (void)hipGetLastError();

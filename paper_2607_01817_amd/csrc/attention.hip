@@ -1295,9 +1295,12 @@ int attention_blocks_per_cu(int d) { return d == 128 ? Shape<128>::PER_CU : Shap
 
 int64_t attention_split_slot_bytes() { return dma::kStashB + 256 * int64_t{sizeof(float4)}; }   // ml: 4 KiB
 
-bool attention_splits_by_segments(int64_t W, int S, int d, int dtype, const SplitScratch *split) {
-    return kLdsDma && d == dma::kD && dtype == 0 &&
-           plan_split(W, (S + kBC - 1) / kBC, split->n_cu, split).ways > 1;
+bool attention_may_split_by_segments(int64_t W, int S, int d, int dtype, const SplitScratch *split) {
+    if (!(kLdsDma && d == dma::kD && dtype == 0)) return false;
+    const int64_t t = split_tiles(W, split->n_cu, split), rem = std::min(t, W);
+    for (const SplitForm &f : kSplitForms)
+        if (rem > 0 && f.ways > 1 && split_fits(f, t, rem, (S + kBC - 1) / kBC, split->n_cu, split)) return true;
+    return false;
 }
 
 int attention_split_ways(int64_t W, int S, int d, int dtype, int n_cu) {
@@ -1344,9 +1347,6 @@ hipError_t launch_attention_riding(const void *q, const void *k, const void *v, 
         return launch_attention(q, k, v, o, lse, S, n_heads, d, scale_log2e, dtype, split, stream);
     using Sh = Shape<dma::kD>;
     const int64_t n_qtiles = (S + Sh::BR - 1) / Sh::BR;
-    const TailSplit t = plan_split(n_qtiles * n_heads, (S + kBC - 1) / kBC, n_cu, split);
-    const int64_t n_attn = static_cast<int64_t>(t.n_whole) + t.units();
-    const int64_t idle = (n_cu - n_attn % n_cu) % n_cu;
     Riders r{};
     r.S = S;
     r.H = H;
@@ -1371,10 +1371,13 @@ hipError_t launch_attention_riding(const void *q, const void *k, const void *v, 
         jb.blocks = static_cast<unsigned>(blocks);
         total += blocks;
     }
-    // Too few idle CUs, or more copy blocks than the 32-bit rider loop
-    // counts: the caller launches the copies itself.
-    if (idle < std::max(1, n_cu / 8) || total >= (int64_t{1} << 31) ||
-        n_attn + idle > 0x7fffffff)
+    const RidingSplit rs = plan_riding(n_qtiles * n_heads, (S + kBC - 1) / kBC, n_cu, split,
+                                       static_cast<double>(total) * copy::kUnitsPerBlock * 16, n_copies);
+    const TailSplit &t = rs.split;
+    const int64_t n_attn = static_cast<int64_t>(t.n_whole) + t.units(), idle = idle_cus(t, n_cu);
+    // Not worth it, or more copy blocks than the 32-bit rider loop counts: the
+    // caller launches the copies itself.
+    if (!rs.ride || total >= (int64_t{1} << 31) || n_attn + idle > 0x7fffffff)
         return launch_attention(q, k, v, o, lse, S, n_heads, d, scale_log2e, dtype, split, stream);
     attention_dma_kernel<true><<<static_cast<unsigned>(n_attn + idle), 64 * dma::kWaves, 0, stream>>>(
         static_cast<const __bf16 *>(q), static_cast<const __bf16 *>(k), static_cast<const __bf16 *>(v),

@@ -51,8 +51,8 @@ int attention_blocks_per_cu(int d);
 
 // Bytes of a partial state of SplitScratch (split_plan.h).
 int64_t attention_split_slot_bytes();
-// Whether a launch of W tiles splits some of them by segments in this scratch.
-bool attention_splits_by_segments(int64_t W, int S, int d, int dtype, const SplitScratch *split);
+// Whether a launch of W tiles may split some of them by segments in this scratch.
+bool attention_may_split_by_segments(int64_t W, int S, int d, int dtype, const SplitScratch *split);
 // Workgroups per split tile of the time model and of the mode rule, for a
 // launch of W tiles on n_cu CUs: 3 or 2 where the last round's W mod n_cu
 // tiles, shared by so many workgroups each, fit in one round, else 1.  (The
@@ -83,8 +83,9 @@ struct RidingCopy {
 // extra workgroups after the attention workgroups, as many as the launch's
 // last round leaves CUs idle on n_cu CUs (H: heads of the [S][H][d] side).
 // Sets *riding when it did so; otherwise (not d = 128 bf16, fewer than
-// n_cu / 8 idle CUs, or copies too large) it launches only the attention and
-// the caller launches the copies after it.  A rider copy and the attention it
+// n_cu / 8 idle CUs, copies too large, or copies that take less time behind
+// the launch: plan_riding) it launches only the attention and the caller
+// launches the copies after it.  A rider copy and the attention it
 // rides with must not touch the same bytes.
 hipError_t launch_attention_riding(const void *q, const void *k, const void *v, void *o, float *lse,
                                    int S, int n_heads, int d, float scale_log2e, int dtype,

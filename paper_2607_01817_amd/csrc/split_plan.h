@@ -149,21 +149,27 @@ struct TailSplit {
 // than 5/8 of a round.  With sp->tail >= 0, t is that and the last
 // min(tail, W) tiles are split: a launch whose last round is shared with
 // another stream's launch splits the tiles that close the pooled rounds.
-inline TailSplit plan_split(int64_t W, int nkb, int n_cu, const SplitScratch *sp) {
+struct SplitForm {
+    int halves, ways, rounds;   // rounds that the shares may take
+};
+inline constexpr SplitForm kSplitForms[] = {{2, 3, 1}, {1, 3, 1}, {2, 1, 1}, {1, 3, 2}, {1, 1, 1}};
+
+// Tiles of the last round, which the launch may share.
+inline int64_t split_tiles(int64_t W, int n_cu, const SplitScratch *sp) {
+    return n_cu < 2 ? 0 : sp && sp->tail >= 0 ? sp->tail : W % n_cu;
+}
+// Whether a last round of t tiles (rem of them this launch's) can take form f.
+inline bool split_fits(SplitForm f, int64_t t, int64_t rem, int nkb, int n_cu, const SplitScratch *sp) {
+    if (f.halves * f.ways * t > int64_t{f.rounds} * n_cu) return false;
+    if (f.rounds == 2 && nkb < (8 * t <= 5 * int64_t{n_cu} ? 40 : 64)) return false;
+    return f.ways == 1 || (sp && sp->part && nkb >= kKeySegmentMinBlocks &&
+                           rem * f.halves * f.ways <= sp->slots && rem * f.halves <= sp->counters);
+}
+inline TailSplit split_as(SplitForm f, int64_t W, int64_t rem, const SplitScratch *sp) {
     TailSplit p{nullptr, nullptr, nullptr, static_cast<int>(W), 0, 1, 1};
-    const int64_t n = n_cu;
-    if (n < 2) return p;
-    const int64_t t = sp && sp->tail >= 0 ? sp->tail : W % n, rem = std::min(t, W);
-    if (rem == 0) return p;
-    auto scratch = [&](int halves) {
-        return sp && sp->part && nkb >= kKeySegmentMinBlocks && rem * halves * kKeySegments <= sp->slots &&
-               rem * halves <= sp->counters;
-    };
-    if (6 * t <= n && scratch(2)) p.halves = 2, p.ways = 3;
-    else if (3 * t <= n && scratch(1)) p.ways = 3;
-    else if (2 * t <= n) p.halves = 2;
-    else if (3 * t <= 2 * n && nkb >= (8 * t <= 5 * n ? 40 : 64) && scratch(1)) p.ways = 3;
-    else return p;
+    if (f.halves * f.ways == 1) return p;
+    p.halves = f.halves;
+    p.ways = f.ways;
     if (p.ways > 1) {
         p.part = static_cast<char *>(sp->part);
         p.ml = static_cast<char *>(sp->ml);
@@ -172,6 +178,73 @@ inline TailSplit plan_split(int64_t W, int nkb, int n_cu, const SplitScratch *sp
     p.n_whole = static_cast<int>(W - rem);
     p.n_split = static_cast<int>(rem);
     return p;
+}
+inline TailSplit plan_split(int64_t W, int nkb, int n_cu, const SplitScratch *sp) {
+    const int64_t t = split_tiles(W, n_cu, sp), rem = std::min(t, W);
+    if (rem > 0)
+        for (const SplitForm &f : kSplitForms)
+            if (split_fits(f, t, rem, nkb, n_cu, sp)) return split_as(f, W, rem, sp);
+    return split_as(SplitForm{1, 1, 1}, W, 0, sp);
+}
+
+// Compute units that the last round of a launch of these tiles leaves idle.
+inline int64_t idle_cus(const TailSplit &p, int n_cu) {
+    const int64_t units = int64_t{p.n_whole} + p.units();
+    return (n_cu - units % n_cu) % n_cu;
+}
+
+// About how long a last round of t tiles takes in form f, in full rounds
+// (those run at a lower clock: 160 whole tiles take 0.75 of 256), and, for S =
+// 64 nkb keys, how long a full round takes in us.  Launches of 16 to 170 tiles
+// of S = 2048 to 75776: six workgroups a tile 0.18 to 0.25, thirds 0.26 (40
+// tiles) to 0.36 (80), halves 0.47 to 80 tiles and 0.58 with 128, thirds over
+// two rounds 0.64 to 0.72, whole 0.73 to 0.77; 256 tiles of S = 4096 127 us,
+// of S = 65536 1700.
+inline double form_rounds(SplitForm f, int64_t t, int n_cu) {
+    const double x = static_cast<double>(t) / n_cu;
+    if (f.ways == 3 && f.halves == 2) return 0.20 + 0.3 * x;
+    if (f.ways == 3 && f.rounds == 1) return 0.26 + 0.3 * x;
+    if (f.halves == 2) return 0.47 + 0.53 * std::max(0.0, x - 0.31);
+    if (f.ways == 3) return 0.65 + 0.6 * std::max(0.0, x - 0.59);
+    return 0.73 + 0.65 * std::max(0.0, x - 0.59);
+}
+inline double round_us(int nkb) { return 1.65 * nkb + 4.0; }
+
+// The split of a launch that copies could ride in, and whether they do.
+// Copies that ride take no time of their own, but a tail shared by more
+// workgroups leaves them fewer CUs and ends earlier.  Of the forms that fit,
+// riding or not, the one expected to end first.  Fitted to the fused and the
+// serial plan of 85 chunkings of S = 3000 to 37000 (within 2 % of the pass):
+// a copy kernel moves 6.5 TB/s, read and written, and takes 1 us more, an idle
+// CU copies 12 GB/s.  Two chunks of 12 heads of S = 3178 take 174 us with
+// whole tiles, 199 with the segments over two rounds that a launch without
+// copies takes.
+struct RidingSplit {
+    TailSplit split;
+    bool ride;
+};
+inline RidingSplit plan_riding(int64_t W, int nkb, int n_cu, const SplitScratch *sp, double copy_bytes,
+                               int n_copies) {
+    RidingSplit best{plan_split(W, nkb, n_cu, sp), false};
+    const int64_t t = split_tiles(W, n_cu, sp), rem = std::min(t, W);
+    if (rem == 0) return best;
+    double t_best = 0;
+    bool first = true;
+    for (const SplitForm &f : kSplitForms) {
+        if (!split_fits(f, t, rem, nkb, n_cu, sp)) continue;
+        const double tail = form_rounds(f, t, n_cu) * round_us(nkb);
+        if (first) t_best = tail + 2 * copy_bytes / 6.5e6 + n_copies;   // the copies behind it
+        first = false;
+        const TailSplit p = split_as(f, W, rem, sp);
+        const int64_t idle = idle_cus(p, n_cu);
+        if (idle < std::max(1, n_cu / 8)) continue;
+        const double end = std::max(tail, tail * (f.rounds - 1) / f.rounds + copy_bytes / (12e3 * idle));
+        if (end < t_best) {
+            t_best = end;
+            best = RidingSplit{p, true};
+        }
+    }
+    return best;
 }
 
 }  // namespace hcms

@@ -14,6 +14,7 @@ using namespace hcms;
 constexpr int64_t kSlot = 68 * 1024;
 // region mem r n_cu            -> part ml count (offsets), slots counters n_cu
 // plan W nkb n_cu mem r tail   -> n_whole n_split halves ways has_scratch
+// copies W nkb n_cu mem r bytes -> n_whole n_split halves ways ride idle, two copies of these bytes
 // use stream role capturing    -> region wait record, a launch of one pool
 int main() {
     char what[16];
@@ -26,6 +27,12 @@ int main() {
             const SplitScratch s = split_region(reinterpret_cast<void *>(mem), r, n_cu, kSlot);
             std::printf("%lld %lld %lld %d %d %d\n", (long long)s.part - mem, (long long)s.ml - mem,
                         (long long)s.count - mem, s.slots, s.counters, s.n_cu);
+        } else if (what[0] == 'c') {
+            if (std::scanf("%lld %d %d %lld %d %lld", &W, &nkb, &n_cu, &mem, &r, &tail) != 6) return 1;
+            const SplitScratch s = split_region(reinterpret_cast<void *>(mem), r, n_cu, kSlot);
+            const RidingSplit p = plan_riding(W, nkb, n_cu, &s, static_cast<double>(tail), 2);
+            std::printf("%d %d %d %d %d %lld\n", p.split.n_whole, p.split.n_split, p.split.halves, p.split.ways,
+                        p.ride, (long long)idle_cus(p.split, n_cu));
         } else if (what[0] == 'u') {
             int role, capturing;
             if (std::scanf("%lld %d %d", &mem, &role, &capturing) != 3) return 1;
@@ -126,6 +133,34 @@ def test_two_rounds_of_segments_only_where_they_are_shorter(rules):
     for (t, nkb), (whole, split, halves, ways, _) in zip(asked, got):
         shared = t <= 170 and nkb >= (40 if t <= 160 else 64)
         assert (whole, split, halves, ways) == ((256, t, 1, 3) if shared else (256 + t, 0, 1, 1)), (t, nkb)
+
+
+@pytest.mark.parametrize("W,nkb,mb,want", [
+    (440, 878, 100, (440, 0, 1, 1, 1)),      # 72 CUs idle over a long whole round
+    (156, 50, 29, (156, 0, 1, 1, 1)),        # whole tiles leave 100 CUs, segments over two rounds 44
+    (411, 1644, 100, (256, 155, 1, 3, 1)),   # long keys: two rounds, and time for the copies in the second
+    (296, 32, 20, (256, 40, 1, 3, 1)),       # thirds leave 136 CUs, sixths 16
+    (296, 32, 77, (256, 40, 2, 1, 1)),       # more copies than 136 CUs move meanwhile: halves leave 176
+    (296, 1184, 100, (256, 40, 2, 3, 0)),    # long keys: sixths, the copies behind them
+    (250, 878, 10, (250, 0, 1, 1, 0)),       # 6 CUs idle
+    (384, 16, 200, (256, 128, 2, 1, 0)),     # more copies than the idle CUs can move meanwhile
+    (512, 878, 100, (512, 0, 1, 1, 0)),      # none idle
+])
+def test_split_of_a_launch_with_copies(rules, W, nkb, mb, want):
+    """Worked by hand from the rates beside plan_riding."""
+    assert rules([f"copies {W} {nkb} 256 {MEM} 0 {mb * 10 ** 6}"])[0][:5] == want
+
+
+@pytest.mark.parametrize("mem", [0, MEM])
+def test_copies_ride_beside_at_least_an_eighth_of_the_units(rules, mem):
+    asked = [(W, nkb, mb) for W in range(1, 520, 3) for nkb in (8, 20, 60, 900) for mb in (1, 30, 400)]
+    got = rules([f"copies {W} {nkb} 256 {mem} 0 {mb * 10 ** 6}" for W, nkb, mb in asked])
+    plain = rules([f"plan {W} {nkb} 256 {mem} 0 -1" for W, nkb, mb in asked])
+    assert any(g[4] for g in got[:len(asked)])
+    for (W, nkb, mb), (whole, split, halves, ways, ride, idle), p in zip(asked, got, plain):
+        assert whole + split == W and (mem or ways == 1)
+        assert idle >= 32 if ride else (whole, split, halves, ways) == p[:4]
+        assert ways == 1 or (nkb >= 12 and split * halves * ways <= 512)
 
 
 def _uses(rules, uses):
