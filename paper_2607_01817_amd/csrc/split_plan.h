@@ -148,7 +148,10 @@ struct TailSplit {
 // against 51 at 1536, so it is taken from 40 key blocks on, from 64 with more
 // than 5/8 of a round.  With sp->tail >= 0, t is that and the last
 // min(tail, W) tiles are split: a launch whose last round is shared with
-// another stream's launch splits the tiles that close the pooled rounds.
+// another stream's launch splits the tiles that close the pooled rounds, and
+// not over two rounds, since both launches' shares are in them: in lanes
+// {11, 10} of S = 4971 took 339 us so, 294 with whole tiles, {4, 4} of S =
+// 12986 747 and 649; of 36 such chunkings 8 were faster so, by up to 3 %.
 struct SplitForm {
     int halves, ways, rounds;   // rounds that the shares may take
 };
@@ -161,7 +164,7 @@ inline int64_t split_tiles(int64_t W, int n_cu, const SplitScratch *sp) {
 // Whether a last round of t tiles (rem of them this launch's) can take form f.
 inline bool split_fits(SplitForm f, int64_t t, int64_t rem, int nkb, int n_cu, const SplitScratch *sp) {
     if (f.halves * f.ways * t > int64_t{f.rounds} * n_cu) return false;
-    if (f.rounds == 2 && nkb < (8 * t <= 5 * int64_t{n_cu} ? 40 : 64)) return false;
+    if (f.rounds == 2 && ((sp && sp->tail >= 0) || nkb < (8 * t <= 5 * int64_t{n_cu} ? 40 : 64))) return false;
     return f.ways == 1 || (sp && sp->part && nkb >= kKeySegmentMinBlocks &&
                            rem * f.halves * f.ways <= sp->slots && rem * f.halves <= sp->counters);
 }

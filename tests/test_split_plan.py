@@ -133,6 +133,9 @@ def test_two_rounds_of_segments_only_where_they_are_shorter(rules):
     for (t, nkb), (whole, split, halves, ways, _) in zip(asked, got):
         shared = t <= 170 and nkb >= (40 if t <= 160 else 64)
         assert (whole, split, halves, ways) == ((256, t, 1, 3) if shared else (256 + t, 0, 1, 1)), (t, nkb)
+    # Not where two launches share the rounds.
+    asked = [(t, r) for t in (129, 160, 170) for r in (0, 1)]
+    assert rules([f"plan 256 900 256 {MEM} {r} {t}" for t, r in asked])[:len(asked)] == [(256, 0, 1, 1, 0)] * 6
 
 
 @pytest.mark.parametrize("W,nkb,mb,want", [
