@@ -323,11 +323,18 @@ HCMS_API int hcms_plan(int n_chunks, int mode, hcms_op *ops, int cap);
  * sum_c ceil(W_c / (n_cu * B)) rounds of workgroups; two lanes pool them,
  * ceil(sum_c W_c / (n_cu * B)).  A launch's last round leaves
  * n_cu * B * ceil(W_c / (n_cu * B)) - W_c slots idle.  Returns
- * HCMS_MODE_SERIAL for one chunk; HCMS_MODE_LANES when pooling saves rounds,
- * rounds saved * S >= 8192 (d = 128 with bf16 storage, whose launches also
- * share the tiles of their partial rounds: lanes only if part of a round is
- * saved after that) or 1536 (shorter rounds cost less than the lanes'
- * synchronisations); otherwise, for d = 128 with bf16 storage, HCMS_MODE_FUSED when some launch
+ * HCMS_MODE_SERIAL for one chunk; HCMS_MODE_LANES when pooling saves enough
+ * rounds: rounds saved * S >= 1536 (shorter rounds cost less than the lanes'
+ * synchronisations).  With d = 128 and bf16 storage, whose launches share the
+ * tiles of their partial rounds, what counts is what is saved after that, at
+ * least 1000 / S rounds: a last round of t tiles counts 0.25 with 6 t <= n_cu,
+ * 0.33 with 3 t <= n_cu, 0.67 with 2 t <= n_cu, 0.9 where its tiles are shared
+ * over two rounds (not in lanes), else 1 (S of fewer than 12 key blocks of 64:
+ * 0.67 or 1), and lanes last no less than the whole rounds of either lane's
+ * launches; chunks that together fill at most one round need rounds saved * S
+ * >= 8192 and some of it left.  Otherwise, for d = 128 with bf16 storage,
+ * HCMS_MODE_FUSED when some launch, its partial round's tiles shared 3 ways
+ * where 3 t <= n_cu and 2 ways where 2 t <= n_cu,
  * leaves at least n_cu * B / 8 slots idle (where the neighbouring chunks'
  * copies ride) and HCMS_MODE_SERIAL when none does (the fused plan would run
  * the serial plan's launches); for the other kernels HCMS_MODE_INLINE when

@@ -342,13 +342,15 @@ int hcms::auto_plan(int S, int d, int dtype, const int *sizes, int C, int n_cu, 
     const int64_t tiles = (S + br - 1) / br;
     int64_t rounds = 0, total = 0;
     double shared = 0;            // rounds, partial ones as long as sharing leaves them
+    int64_t lane[2] = {0, 0};     // whole rounds of each lane's launches, one after the other
     bool some_idle = false;       // a launch whose last round leaves enough slots idle
     bool first_idle = false;      // ... for chunk 0's launch in particular
     for (int c = 0; c < C; ++c) {
         const int64_t wc = tiles * sizes[c];
         rounds += (wc + slots - 1) / slots;
+        lane[c % 2] += (wc + slots - 1) / slots;
         total += wc;
-        shared += wc / slots + hcms::attention_partial_round(wc % slots, S, n_cu);
+        shared += wc / slots + hcms::attention_partial_round(wc % slots, S, n_cu, false);
         // The workgroups the launch runs: its last round's tiles may be split.
         const int64_t rem = wc % slots;
         const int64_t run = wc - rem + rem * hcms::attention_split_ways(wc, S, d, dtype, n_cu);
@@ -361,18 +363,25 @@ int hcms::auto_plan(int S, int d, int dtype, const int *sizes, int C, int n_cu, 
     // 0.02 us per key, for four synchronisations of 6 us and launches that
     // start later.  Below lanes_keys the plans without any are faster: two
     // chunks of S = 512 61 us in lanes, 36 serial; {4, 4} of S = 3001 88 in
-    // lanes, 78 fused, {5, 4, 4} of S = 6000 326 and 303; but fp32 {3, 2} of S = 3075, d = 64, in two slots 95 in
+    // lanes, 78 fused; but fp32 {3, 2} of S = 3075, d = 64, in two slots 95 in
     // lanes, 126 serial (S = 32760 {5, 5}: lanes 4.3 ms, fused 4.7).
-    // Where the kernel shares the tiles of its partial rounds, lanes have to
-    // save a part of a round after that too: {2, 2, 2, 2} of S = 9610, 4
-    // thirds of a round either way, 483 us in lanes, 419 fused.  The backward
-    // shares none, and its rounds last several times as long.
+    // Where the kernel shares the tiles of its partial rounds, what counts is
+    // what lanes save after that, and no lane ends before its own launches,
+    // which do not share: {8, 7, 7} of S = 5463, 2.8 rounds in 1.9, takes 348
+    // us in lanes, 396 fused; {7, 7, 7} of S = 3390, three rounds of halves,
+    // 212 and 193; {2, 2, 2, 2} of S = 9610, four of thirds, 483 and 419.  100
+    // chunkings of S = 3000 to 40000 that the rule was not made with take 1.2 %
+    // longer than in the better plan, at worst 11 %.
+    // The backward shares none, and its rounds last several times as long.
     const int64_t saved = rounds - (total + slots - 1) / slots;
     const bool shares = !backward && d == 128 && dtype == HCMS_BF16;
-    const int64_t lanes_keys = backward ? 512 : shares ? 8192 : 1536;
-    if (saved > 0 && saved * S >= lanes_keys &&
-        (!shares || shared > total / slots + hcms::attention_partial_round(total % slots, S, n_cu) + 0.01))
-        return HCMS_MODE_LANES;
+    const double pooled = static_cast<double>(total / slots) +
+                          hcms::attention_partial_round(total % slots, S, n_cu, true);
+    const double less = shared - std::max(pooled, static_cast<double>(std::max(lane[0], lane[1])));
+    const int64_t lanes_keys = backward ? 512 : 1536;
+    const bool lanes = !shares ? saved * S >= lanes_keys
+                       : total > slots ? less * S >= 1000 : saved * S >= 8192 && shared > pooled + 0.01;
+    if (saved > 0 && lanes) return HCMS_MODE_LANES;
     // The fused plan moves copies only on CUs a launch's last round leaves
     // idle; with none anywhere it would run the serial plan's launches.
     if (d == 128 && dtype == HCMS_BF16) return some_idle ? HCMS_MODE_FUSED : HCMS_MODE_SERIAL;

@@ -1310,15 +1310,16 @@ int attention_split_ways(int64_t W, int S, int d, int dtype, int n_cu) {
     return 3 * rem <= n_cu ? 3 : 2 * rem <= n_cu ? 2 : 1;
 }
 
-double attention_partial_round(int64_t t, int S, int n_cu) {
+double attention_partial_round(int64_t t, int S, int n_cu, bool pooled) {
     if (t == 0) return 0;
     SplitScratch sp{};
     sp.part = sp.ml = reinterpret_cast<void *>(uintptr_t{256});   // placeholders: never dereferenced
     sp.n_cu = n_cu;
     sp.slots = sp.counters = 2 * n_cu;
+    sp.tail = pooled ? t : -1;
     const TailSplit p = plan_split(t, (S + kBC - 1) / kBC, n_cu, &sp);
-    if (p.ways == 3) return p.halves == 2 ? 0.25 : 3 * t <= n_cu ? 0.33 : 0.67;
-    return p.halves == 2 ? 0.75 : 1;
+    if (p.ways == 3) return p.halves == 2 ? 0.25 : 3 * t <= n_cu ? 0.33 : 0.9;
+    return p.halves == 2 ? 0.67 : 1;
 }
 
 hipError_t launch_attention(const void *q, const void *k, const void *v, void *o, float *lse, int S,

@@ -59,8 +59,9 @@ bool attention_may_split_by_segments(int64_t W, int S, int d, int dtype, const S
 // launch itself may share them further: halves of a tile, two rounds.)
 int attention_split_ways(int64_t W, int S, int d, int dtype, int n_cu);
 // About how long a d = 128 bf16 launch's last round of t < n_cu tiles takes,
-// in rounds, with the tiles shared as the launch does.
-double attention_partial_round(int64_t t, int S, int n_cu);
+// in rounds, with the tiles shared as the launch does.  pooled: the tiles past
+// the last whole round of two lanes.
+double attention_partial_round(int64_t t, int S, int n_cu, bool pooled);
 
 // lse, if not NULL, receives [n_heads][S] fp32 log2 softmax denominators:
 // P_ij = exp2(scale_log2e * <q_i, k_j> - lse_i).  split: NULL, or scratch

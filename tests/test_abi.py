@@ -709,3 +709,19 @@ def test_auto_mode_of_short_rounds(lib, S, d, sizes, want):
              "fused": hcms.MODE_FUSED}
     assert hcms.auto_mode(S, d, sizes, 256) == modes[want[0]]
     assert hcms.auto_mode(S, d, sizes, 256, dtype=hcms.FP32) == modes[want[1]]
+
+
+@pytest.mark.parametrize("S,sizes,want", [
+    (5463, (8, 7, 7), "lanes"),         # 176, 154, 154 tiles: 1 + 0.9 + 0.9, pooled 484 tiles 2
+    (5609, (7, 7, 7), "lanes"),         # 3 x 0.9, pooled 2
+    (8035, (6,) * 4, "lanes"),          # 192 tiles each: 4, pooled 3
+    (3390, (7, 7, 7), "fused"),         # 98 tiles: 3 x 0.67, lane 0 runs two launches
+    (15857, (2, 1, 1, 1), "fused"),     # 0.67 + 3 x 0.33, two launches a lane
+    (5114, (4, 4, 3, 3), "fused"),      # 80, 80, 60, 60: 4 x 0.33
+    (12024, (4, 4, 3), "fused"),        # 188, 188, 141: no round saved
+    (12986, (4, 4), "fused"),           # 204 each: 2 x 2 rounds, pooled 4
+])
+def test_auto_mode_counts_shared_rounds(lib, S, sizes, want):
+    """Partial rounds count as long as sharing leaves them, in one lane and
+    pooled, and a lane's launches run one after the other."""
+    assert hcms.auto_mode(S, 128, sizes, 256) == {"lanes": hcms.MODE_LANES, "fused": hcms.MODE_FUSED}[want]
