@@ -20,6 +20,7 @@ import torch
 
 from paper_2607_01817_amd import inputs
 from oracle import layer as olayer
+from tests import gemm_shapes as gs
 from tests.gpu_util import bits, log
 
 pytestmark = pytest.mark.gpu
@@ -205,18 +206,13 @@ def test_layer_forward_is_the_three_calls(hcms):
     assert torch.equal(bits(y.cpu()), bits(y2.cpu()))
 
 
-@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
-@pytest.mark.parametrize("M,N,K", [
-    (65, 72, 64), (130, 1032, 1024),                          # 64 x 64, one stage and many
-    (1025, 1928, 256), (1025, 15368, 64),                     # 128 x 128 and its remainders
-    (70, 15368, 512),                                         # 64 x 128, few rows
-    (3001, 3008, 64), (3065, 4104, 320), (2000, 4880, 192),   # 192 x 256, 256 x 192
-    (4001, 4008, 64), (4100, 8200, 192)])                     # 256 x 256, one round and more
-def test_linear_tiles_match_oracle(hcms, M, N, K, dtype):
-    """Every tile of the GEMM on 256 compute units, with ragged rows and
-    columns and reductions of one stage, odd and even counts.  One rounding of
-    the exact product: bounds as in test_linear_matches_oracle."""
-    log(f"[linear tiles] M={M} N={N} K={K} {dtype}")
+def _dtype(elem_bytes):
+    return torch.bfloat16 if elem_bytes == gs.BF16 else torch.float32
+
+
+def _check_linear(hcms, M, N, K, dtype):
+    """Sampled rows against the oracle: one rounding of the exact product,
+    bounds as in test_linear_matches_oracle."""
     g = torch.Generator().manual_seed(M + N + K)
     x = torch.randn(M, K, generator=g).to(dtype)
     w = (torch.randn(N, K, generator=g) / K ** 0.5).to(dtype)
@@ -228,12 +224,32 @@ def test_linear_tiles_match_oracle(hcms, M, N, K, dtype):
 
 
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("M,N,K", [
+    (65, 72, 64), (130, 1032, 1024), (1025, 1928, 256), (1025, 15368, 64), (70, 15368, 512),
+    (3001, 3008, 64), (3065, 4104, 320), (2000, 4880, 192), (4001, 4008, 64), (4100, 8200, 192)])
+def test_linear_tiles_match_oracle(hcms, M, N, K, dtype):
+    """Ragged rows and columns, small and large outputs, reductions of one
+    stage, odd and even counts."""
+    log(f"[linear tiles] M={M} N={N} K={K} {dtype}")
+    _check_linear(hcms, M, N, K, dtype)
+
+
+@pytest.mark.parametrize("tile,more,elem_bytes,M,N,K", gs.LINEAR)
+def test_linear_on_every_tile(hcms, tile, more, elem_bytes, M, N, K):
+    """Each tile of the GEMM, in one round of workgroups and in more (the host
+    test of the tile rule checks that these shapes take it)."""
+    log(f"[linear] tile {tile} rounds>1={more} M={M} N={N} K={K} {elem_bytes} bytes")
+    assert torch.cuda.get_device_properties(0).multi_processor_count == 256
+    _check_linear(hcms, M, N, K, _dtype(elem_bytes))
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("S,D,H,d", [(97, 64, 3, 8), (1301, 192, 5, 128), (3001, 128, 8, 128),
                                      (2600, 64, 13, 128), (4100, 128, 10, 128)])
 def test_qkv_tiles_match_linear(hcms, S, D, H, d, dtype):
-    """The split of the QKV epilogue on every tile, at head boundaries inside
-    and across segments: without a rotation q, k, v hold the bits of the plain
-    product's columns."""
+    """The split of the QKV epilogue at head boundaries inside and across
+    segments: without a rotation q, k, v hold the bits of the plain product's
+    columns."""
     log(f"[qkv tiles] S={S} D={D} H={H} d={d} {dtype}")
     g = torch.Generator().manual_seed(S + D)
     x = torch.randn(S, D, generator=g).to(dtype).cuda()
@@ -241,3 +257,27 @@ def test_qkv_tiles_match_linear(hcms, S, D, H, d, dtype):
     qkv = torch.stack(hcms.qkv_projection(x, w, H, d), dim=1)
     plain = hcms.linear(x, w).view(S, 3, H, d)
     assert torch.equal(bits(qkv.cpu()), bits(plain.cpu()))
+
+
+@pytest.mark.parametrize("tile,more,elem_bytes,grid,D,H,d", gs.QKV)
+def test_qkv_on_every_tile(hcms, tile, more, elem_bytes, grid, D, H, d):
+    """The split and the rotation of the QKV epilogue on each tile, in one round
+    of workgroups and in more: the unrotated features hold the bits of the plain
+    product, the rotated ones of sampled tokens are the oracle's."""
+    S, dtype = grid[0] * grid[1], _dtype(elem_bytes)
+    log(f"[qkv] tile {tile} rounds>1={more} S={S} D={D} H={H} d={d} {elem_bytes} bytes")
+    assert torch.cuda.get_device_properties(0).multi_processor_count == 256
+    g = torch.Generator().manual_seed(S + D + H)
+    x = torch.randn(S, D, generator=g).to(dtype)
+    w = (torch.randn(3 * H * d, D, generator=g) / D ** 0.5).to(dtype)
+    pairs = (d // 2 - 22, 22)
+    q, k, v = hcms.qkv_projection(x.cuda(), w.cuda(), H, d, hcms.rope_table(grid, pairs, 10000.0), grid, pairs)
+    plain = hcms.linear(x.cuda(), w.cuda()).view(S, 3, H, d)
+    unrotated = torch.stack(hcms.qkv_projection(x.cuda(), w.cuda(), H, d), dim=1)
+    assert torch.equal(bits(unrotated), bits(plain)) and torch.equal(bits(v.contiguous()), bits(plain[:, 2].contiguous()))
+    rows = np.unique(np.concatenate([np.arange(0, S, max(1, S // 61)), [S - 1]]))
+    wq, wk, _ = olayer.split_qkv(olayer.linear(_f64(x[rows]), _f64(w).T), H, d)
+    ang = olayer.rope_angles(grid, pairs, 10000.0)[rows]
+    rel = 2.0 ** -8 if dtype == torch.bfloat16 else 2.0 ** -7
+    for nm, got, want in (("q", q, wq), ("k", k, wk)):
+        _check_close(_f64(got.cpu()[rows]), olayer.rope(want, ang), nm, rel)
