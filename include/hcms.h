@@ -14,7 +14,7 @@
  * Conventions for every entry point
  *   - Buffers are device memory owned by the caller, contiguous, row-major,
  *     16-byte aligned.  The library allocates no device memory on any call
- *     except hcms_ctx_create (events, and 68 MiB to share tiles in).
+ *     except hcms_ctx_create (events, and 64 MiB to share tiles in).
  *   - `stream` arguments are hipStream_t handles passed as void*.  NULL is the
  *     null stream of the current device.  Streams are borrowed, never destroyed.
  *   - All compute calls are asynchronous and stream-ordered; a kernel fault

@@ -31,10 +31,11 @@ struct SplitScratch {
     int64_t tail = -1;
 };
 
-// A context's scratch: region 0 of 2 n_cu slots and regions 1 and 2 of n_cu,
-// as many counters each.
+// A context's scratch: regions of 2 n_cu, n_cu and 3/4 n_cu slots, as many
+// counters each.  On 256 CUs that is 63.8 MiB: an allocation of more than 64
+// takes 27 us, and 260 to free, 11 and 20 up to there.
 inline constexpr int kSplitRegions = 3;
-inline int split_slots(int r, int n_cu) { return r == 0 ? 2 * n_cu : n_cu; }
+inline int split_slots(int r, int n_cu) { return r == 0 ? 2 * n_cu : r == 1 ? n_cu : n_cu * 3 / 4; }
 inline int64_t split_slots_before(int r, int n_cu) {
     int64_t n = 0;
     for (int i = 0; i < r; ++i) n += split_slots(i, n_cu);

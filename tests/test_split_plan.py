@@ -89,7 +89,7 @@ def test_regions_fill_the_scratch_without_overlap(rules):
     for at, n in sorted(spans):
         assert at == end
         end = at + n
-    assert end == total
+    assert end == total < 64 << 20
 
 
 @pytest.mark.parametrize("mem", [0, -1])
@@ -116,7 +116,7 @@ def test_an_unset_scratch_splits_nothing(rules):
 
 @pytest.mark.parametrize("r", [0, 1, 2])
 def test_split_units_fit_the_scratch(rules, r):
-    slots = 512 if r == 0 else 256
+    slots = (512, 256, 192)[r]
     asked = [(W, nkb, tail) for W in range(1, 520) for nkb in (11, 12) for tail in (-1, 0, 40, 76, 170)]
     got = rules([f"plan {W} {nkb} 256 {MEM} {r} {tail}" for W, nkb, tail in asked])
     for (W, nkb, tail), (whole, split, halves, ways, scratch) in zip(asked, got):
