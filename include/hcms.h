@@ -383,10 +383,11 @@ HCMS_API int hcms_model_fit(const int *chunk_counts, const double *times, int n,
  * partial round keeping a fraction f = (W mod n) / n of the slots busy,
  * which lasts t_round (g0 + (1 - g0) f) (the clock rises when part of the
  * chip idles; g0 = 1: a partial round costs a full one).  When the attention
- * kernel splits that round's tiles by key segments (hcms_forward's d = 128
- * bf16 launches; the model counts 3 rem <= n three ways, else 2 rem <= n two
- * ways, with S of 12 key blocks or more, and no further sharing; in the lanes
- * plan the last launch of each lane
+ * kernel shares that round's tiles (hcms_forward's d = 128 bf16 launches; the
+ * model counts 3 rem <= n three ways, by key segments, else 2 rem <= n two
+ * ways, in halves, with S of 12 key blocks or more, and neither further
+ * sharing nor the joining of chunks that fill at most one round, so it times
+ * the shortest launches long; in the lanes plan the last launch of each lane
  * splits the rem = sum W mod n tiles past the pooled rounds) the round holds
  * ways rem workgroups and lasts a third (three ways) or two thirds (two ways)
  * as long.  Every launch on the critical path adds `drain` rounds (its last

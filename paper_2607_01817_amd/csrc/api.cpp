@@ -536,7 +536,7 @@ int check_schedule(hcms_ctx *ctx, int P, int S, int H, int d, float scale, const
 // attention workgroups together fill no more than one round of the CUs, a
 // launch per chunk leaves most of them idle and costs more than any overlap
 // brings (S = 4096, 8 heads in {4, 4}: 104 us as two chunks, 88 joined; S =
-// 512, 4 heads in {2, 2}: 36 and 21).  The results are the same bits: they do
+// 512, 4 heads in {2, 2}: 36 and 18).  The results are the same bits: they do
 // not depend on the chunking.  Not while the context times its launches,
 // which it reports chunk by chunk.
 bool joins_chunks(const hcms_ctx *ctx, int S, int H, int d) {

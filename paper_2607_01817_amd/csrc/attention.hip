@@ -106,7 +106,8 @@ __device__ inline void qk_mfma(f32x16 (&sacc)[NT][2], const __bf16 *ks,
 // kPvAhead MFMAs ahead of their use.  With d = 128 two, not more: the kernel
 // stays within 248 VGPRs, so two waves per SIMD leave 16 registers per lane
 // for the waves of a pack or unpack running beside them.  With d = 64 four (16
-// heads of S = 8192 301 us with two, 295 with four or six, 303 with eight).
+// heads of S = 8192 303 us with two, 298 to 300 with four; six no faster, eight
+// slower).
 template <int D>
 constexpr int kPvAhead = D == 64 ? 4 : 2;
 
@@ -563,8 +564,8 @@ __host__ __device__ inline int seg_begin(int nkb, int g) {
     const int n = n_segments(nkb);
     return g <= 0 ? 0 : g >= n ? nkb : (g * nkb + n / 2) / n;
 }
-// A segment's unnormalised output, rounded to bf16, kept in LDS between
-// segments: 64 values per lane, chunk k (values 8k .. 8k + 7) of lane l of
+// The state of the segments so far, 16 bits per value (state_chunk), kept in
+// LDS between segments: 64 values per lane, chunk k (values 8k .. 8k + 7) of lane l of
 // wave w at byte w * 8 KiB + k * 1 KiB + 16 l.  Partial states of split tiles
 // use the same layout in global memory.
 constexpr int kStashWaveB = 64 * 64 * 2;
@@ -726,7 +727,7 @@ __device__ inline void run_riders(const Riders &r, unsigned rider, unsigned n_ri
 // per value: N scaled by 2^-E, E the binary exponent of the query's largest
 // |N| (over both halves of the wave), rounded to fp16 (nearest-even), so a
 // stored value keeps 11 significant bits relative to the query's largest.
-// quantise applies exactly that rounding in registers; store_state and
+// quantise applies exactly that rounding in registers; state_chunk and
 // load_state move the rounded values through LDS or global memory unchanged.
 __device__ inline int state_exponent(const f32x16 (&n)[4]) {
     float a = 0.f;

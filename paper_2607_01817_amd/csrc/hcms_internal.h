@@ -53,10 +53,11 @@ int attention_blocks_per_cu(int d);
 int64_t attention_split_slot_bytes();
 // Whether a launch of W tiles may split some of them by segments in this scratch.
 bool attention_may_split_by_segments(int64_t W, int S, int d, int dtype, const SplitScratch *split);
-// Workgroups per split tile of the time model and of the mode rule, for a
-// launch of W tiles on n_cu CUs: 3 or 2 where the last round's W mod n_cu
-// tiles, shared by so many workgroups each, fit in one round, else 1.  (The
-// launch itself may share them further: halves of a tile, two rounds.)
+// Workgroups per shared tile of the time model and of the mode rule's idle
+// CUs, for a launch of W tiles on n_cu CUs: 3 or 2 where the last round's W
+// mod n_cu tiles, shared by so many workgroups each, fit in one round, else 1.
+// (A launch that carries no copies may share them further: six ways, or
+// segments over two rounds.)
 int attention_split_ways(int64_t W, int S, int d, int dtype, int n_cu);
 // About how long a d = 128 bf16 launch's last round of t < n_cu tiles takes,
 // in rounds, with the tiles shared as the launch does.  pooled: the tiles past

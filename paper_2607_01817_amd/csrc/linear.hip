@@ -36,9 +36,11 @@
 //     registers: 8192 x 8192 x 8192 took 925 us (1188 TFLOP/s), 56160 x 1920 x
 //     5120 1056, 56160 x 5120 x 640 406; now 797, 942 and
 //     352.  What bounds it now: the power limit (1.7 GHz with the matrix
-//     cores 78 % busy on 8192 x 8192 x 4096, 396 us; an earlier version of
-//     the loop took 411 us, and 382 without any load; an MFMA loop with the
-//     same LDS reads on random operands reaches 1710 TFLOP/s);
+//     cores 78 % busy on 8192 x 8192 x 4096, 396 us; an MFMA loop with the
+//     same LDS reads on random operands reaches 1710 TFLOP/s), and on short
+//     reductions of outputs that the last-level cache does not hold the
+//     writes: 40000 x 4096 x 192 takes 111 us, 107 before, 40000 x 4008 x
+//     192, whose rows begin inside cache lines, 126 and 107;
 //   * tiles are ordered in groups of 8 row tiles (all column tiles of a group
 //     before the next group); workgroups are persistent, each round of the
 //     grid takes the next G tiles of that order, and the 8 XCDs each take a

@@ -18,9 +18,10 @@
 // t_round (g0 + (1 - g0) f) rather than a whole t_round.  Summed over the
 // launches, T_attn = t_round (sum W / n) + t_round g0 (R - sum W / n) with
 // R = sum ceil(W / n) the round count: only the idle share of the partial
-// rounds depends on C.  A launch that splits its last round's tiles by key
-// segments (attention_split_ways) shortens that round to a third or two
-// thirds.  Each launch also drains: its last workgroups finish at different
+// rounds depends on C.  A launch that shares its last round's tiles
+// (attention_split_ways: three ways by key segments, two ways in halves)
+// shortens that round to a third or two thirds; what launches share beyond
+// that, and chunks that hcms_forward joins, the model leaves out.  Each launch also drains: its last workgroups finish at different
 // times (the XCDs run at different clocks), a cost of `drain` rounds per
 // launch on the critical path.  hcms_model_plan_time adds the copies each plan
 // leaves on the critical path and its synchronisations; hcms_choose_chunks
@@ -69,9 +70,9 @@ bool solve3(double m[3][3], double r[3], double x[3]) {
 }
 
 // Duration of one launch of W workgroups on n slots, in units of a full round,
-// when its last round's tiles are split `ways` ways by key segments (1: not
-// split; 2: the round lasts two thirds as long with 2 rem workgroups busy;
-// 3: a third as long with 3 rem busy).
+// when its last round's tiles are shared `ways` ways (1: not shared; 2, in
+// halves: the round lasts two thirds as long with 2 rem workgroups busy; 3, by
+// key segments: a third as long with 3 rem busy).
 double launch_rounds(int64_t W, int64_t n, double g0, int ways) {
     if (W <= 0) return 0.0;
     const int64_t full = W / n, rem = W % n;
