@@ -21,12 +21,12 @@
 // rounds depends on C.  A launch that shares its last round's tiles
 // (attention_split_ways: three ways by key segments, two ways in halves)
 // shortens that round to a third or two thirds; what launches share beyond
-// that, and chunks that hcms_forward joins, the model leaves out.  Each launch also drains: its last workgroups finish at different
-// times (the XCDs run at different clocks), a cost of `drain` rounds per
-// launch on the critical path.  hcms_model_plan_time adds the copies each plan
-// leaves on the critical path and its synchronisations; hcms_choose_chunks
-// picks the chunk count whose plan (the one HCMS_MODE_AUTO runs) the model
-// predicts fastest.
+// that, and chunks that hcms_forward joins, the model leaves out.  Each launch
+// also drains: its last workgroups finish at different times (the XCDs run at
+// different clocks), a cost of `drain` rounds per launch on the critical path.
+// hcms_model_plan_time adds the copies each plan leaves on the critical path
+// and its synchronisations; hcms_choose_chunks picks the chunk count whose
+// plan (the one HCMS_MODE_AUTO runs) the model predicts fastest.
 #include <algorithm>
 #include <cmath>
 #include <vector>
