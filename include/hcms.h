@@ -502,7 +502,9 @@ HCMS_API int hcms_ctx_kernel_ms(hcms_ctx *ctx, int kind, float *ms_out, int cap)
  *   copy_stream, compute_stream: used in pipelined mode; must be distinct from
  *                                each other and from main_stream.  Inline mode
  *                                uses copy_stream only, lanes mode
- *                                compute_stream only (distinct from main);
+ *                                compute_stream only (distinct from main;
+ *                                auto mode without one takes the plan it
+ *                                would take if lanes saved nothing);
  *                                fused mode uses neither.
  * Errors: as hcms_pack and hcms_attention, plus ARG (mode, stream reuse,
  * context of another device) and CHUNKS (n_chunks > the context's max_chunks).

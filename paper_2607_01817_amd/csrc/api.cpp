@@ -335,7 +335,7 @@ int plan_size(int C, int mode) {
 }  // namespace
 
 // The plan HCMS_MODE_AUTO runs (hcms_auto_mode without validation).
-int hcms::auto_plan(int S, int d, int dtype, const int *sizes, int C, int n_cu, bool backward) {
+int hcms::auto_plan(int S, int d, int dtype, const int *sizes, int C, int n_cu, bool backward, bool lanes) {
     if (C == 1) return HCMS_MODE_SERIAL;
     const int64_t br = hcms::attention_queries_per_block(d);
     const int64_t slots = static_cast<int64_t>(n_cu) * hcms::attention_blocks_per_cu(d);
@@ -379,9 +379,9 @@ int hcms::auto_plan(int S, int d, int dtype, const int *sizes, int C, int n_cu, 
                           hcms::attention_partial_round(total % slots, S, n_cu, true);
     const double less = shared - std::max(pooled, static_cast<double>(std::max(lane[0], lane[1])));
     const int64_t lanes_keys = backward ? 512 : 1536;
-    const bool lanes = !shares ? saved * S >= lanes_keys
-                       : total > slots ? less * S >= 1000 : saved * S >= 8192 && shared > pooled + 0.01;
-    if (saved > 0 && lanes) return HCMS_MODE_LANES;
+    const bool faster = !shares ? saved * S >= lanes_keys
+                        : total > slots ? less * S >= 1000 : saved * S >= 8192 && shared > pooled + 0.01;
+    if (lanes && saved > 0 && faster) return HCMS_MODE_LANES;
     // The fused plan moves copies only on CUs a launch's last round leaves
     // idle; with none anywhere it would run the serial plan's launches.
     if (d == 128 && dtype == HCMS_BF16) return some_idle ? HCMS_MODE_FUSED : HCMS_MODE_SERIAL;
@@ -510,7 +510,8 @@ int check_schedule(hcms_ctx *ctx, int P, int S, int H, int d, float scale, const
         (copy_stream == compute_stream || copy_stream == main_stream || compute_stream == main_stream))
         return fail(HCMS_ERR_ARG, "pipelined and slots modes need three distinct streams");
     int r = m != HCMS_MODE_AUTO ? m
-            : hcms::auto_plan(S, d, dtype, chunk_sizes, n_chunks, ctx->n_cu, backward);
+            : hcms::auto_plan(S, d, dtype, chunk_sizes, n_chunks, ctx->n_cu, backward,
+                              compute_stream != main_stream);
     // The backward with stored score gradients: one chunk's HBM-bound dQ
     // product overlaps the next chunk's key-parallel launch in lanes.
     if (m == HCMS_MODE_AUTO && prefer_lanes && n_chunks >= 2 && compute_stream != main_stream)

@@ -45,8 +45,10 @@ inline constexpr unsigned kCopyBesideAttentionLds = 40 * 1024;
 int attention_queries_per_block(int d);
 
 // The plan HCMS_MODE_AUTO runs for these chunks (hcms_auto_mode's rule; the
-// arguments are not validated), or for the backward of these chunks.
-int auto_plan(int S, int d, int dtype, const int *sizes, int C, int n_cu, bool backward = false);
+// arguments are not validated), or for the backward of these chunks; lanes
+// false: on one stream, which lanes cannot run on.
+int auto_plan(int S, int d, int dtype, const int *sizes, int C, int n_cu, bool backward = false,
+              bool lanes = true);
 int attention_blocks_per_cu(int d);
 
 // Bytes of a partial state of SplitScratch (split_plan.h).

@@ -337,6 +337,25 @@ def test_auto_mode_runs_the_predicted_plan(hcms, name, sizes):
     ctx.close()
 
 
+def test_auto_mode_on_one_stream_takes_no_lanes(hcms):
+    """With the main stream in place of the compute stream, an automatic call
+    runs the plan it would run if lanes saved nothing."""
+    S, H, sizes = 5463, 22, (8, 7, 7)
+    g = torch.Generator().manual_seed(S)
+    q, k, v = (torch.randn(S, H, 128, generator=g).to(torch.bfloat16).cuda() for _ in range(3))
+    ctx = hcms.Context()
+    ref = ctx.forward(q, k, v, 1, 128 ** -0.5, sizes, mode=hcms.MODE_AUTO).clone()
+    assert ctx.last_mode == hcms.MODE_LANES
+    ctx.compute_stream = torch.cuda.current_stream()
+    out = ctx.forward(q, k, v, 1, 128 ** -0.5, sizes, mode=hcms.MODE_AUTO)
+    assert ctx.last_mode == hcms.MODE_FUSED
+    assert torch.equal(bits(out), bits(ref))
+    with pytest.raises(hcms.HcmsError):
+        ctx.forward(q, k, v, 1, 128 ** -0.5, sizes, mode=hcms.MODE_LANES)
+    torch.cuda.synchronize()
+    ctx.close()
+
+
 @pytest.mark.parametrize("name,sizes", [("wan_p8", (2, 2, 1)), ("wan_p8", (5,)), ("small", (8,)),
                                         ("small", (3, 3, 2))])
 def test_forward_is_deterministic(hcms, name, sizes):
