@@ -312,6 +312,35 @@ def test_fused_forward_bitwise_equals_serial(hcms, S, H, P, sizes_list):
     ctx.close()
 
 
+# Sequence lengths at which a launch of one head shares its 36, 63, 98 and 145
+# tiles by segments of halves, by segments, in halves and by segments over two
+# rounds, and keeps 184 whole, with the neighbouring chunks' copies riding (the
+# host test of the split plan checks the forms).
+RIDING_FORMS = (9000, 16000, 25000, 37000, 47000)
+
+
+@pytest.mark.parametrize("S", RIDING_FORMS)
+def test_copies_ride_beside_every_form(hcms, S):
+    """The fused plan of three chunks of one head gives the serial plan's bits
+    with workspaces and output poisoned first."""
+    log(f"[riding] S={S}")
+    g = torch.Generator().manual_seed(S)
+    q, k, v = (torch.randn(S, 3, 128, generator=g).to(torch.bfloat16).cuda() for _ in range(3))
+    scale = 128 ** -0.5
+    ctx = hcms.Context(max_chunks=4)
+    ref = ctx.forward(q, k, v, 1, scale, (3,), mode=hcms.MODE_SERIAL).clone()
+    for rep in range(2):
+        ws = ctx.workspaces(S, 3, 128, q.dtype)
+        out = torch.empty_like(q)
+        for t in (*ws, out):
+            _fill_bits(t)
+        torch.cuda.synchronize()
+        ctx.forward(q, k, v, 1, scale, (1, 1, 1), mode=hcms.MODE_FUSED, out=out, workspaces=ws)
+        torch.cuda.synchronize()
+        assert torch.equal(bits(out), bits(ref)), rep
+    ctx.close()
+
+
 @pytest.mark.parametrize("name,sizes", [("wan_p8", (2, 2, 1)), ("wan_p4", (5, 5)),
                                         ("small", (3, 3, 2)), ("small", (8,))])
 def test_auto_mode_runs_the_predicted_plan(hcms, name, sizes):

@@ -148,6 +148,9 @@ def test_two_rounds_of_segments_only_where_they_are_shorter(rules):
     (250, 878, 10, (250, 0, 1, 1, 0)),       # 6 CUs idle
     (384, 16, 200, (256, 128, 2, 1, 0)),     # more copies than the idle CUs can move meanwhile
     (512, 878, 100, (512, 0, 1, 1, 0)),      # none idle
+    # The middle launches of RIDING_FORMS in the GPU tests, three chunks of one head.
+    (36, 141, 9, (0, 36, 2, 3, 1)), (63, 250, 16, (0, 63, 1, 3, 1)), (98, 391, 26, (0, 98, 2, 1, 1)),
+    (145, 579, 38, (0, 145, 1, 3, 1)), (184, 735, 48, (184, 0, 1, 1, 1)),
 ])
 def test_split_of_a_launch_with_copies(rules, W, nkb, mb, want):
     """Worked by hand from the rates beside plan_riding."""
