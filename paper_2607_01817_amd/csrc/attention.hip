@@ -1378,15 +1378,18 @@ hipError_t launch_attention_riding(const void *q, const void *k, const void *v, 
     const TailSplit &t = rs.split;
     const int64_t n_attn = static_cast<int64_t>(t.n_whole) + t.units(), idle = idle_cus(t, n_cu);
     // Not worth it, or more copy blocks than the 32-bit rider loop counts: the
-    // caller launches the copies itself.
-    if (!rs.ride || total >= (int64_t{1} << 31) || n_attn + idle > 0x7fffffff)
-        return launch_attention(q, k, v, o, lse, S, n_heads, d, scale_log2e, dtype, split, stream);
-    attention_dma_kernel<true><<<static_cast<unsigned>(n_attn + idle), 64 * dma::kWaves, 0, stream>>>(
+    // caller launches the copies itself.  With the same kernel: its
+    // instructions and those of the one without copies do not fit the
+    // instruction caches together, and a call that runs both in turn fetches
+    // them anew (three chunks of 12 heads of S = 2153 173 us so, 163 with one).
+    const bool ride = rs.ride && total < (int64_t{1} << 31);
+    const int64_t grid = n_attn + (ride ? idle : 0);
+    if (grid > 0x7fffffff) return hipErrorInvalidValue;
+    attention_dma_kernel<true><<<static_cast<unsigned>(grid), 64 * dma::kWaves, 0, stream>>>(
         static_cast<const __bf16 *>(q), static_cast<const __bf16 *>(k), static_cast<const __bf16 *>(v),
         static_cast<__bf16 *>(o), lse, S, static_cast<int>(n_qtiles), scale_log2e, t, r);
     const hipError_t e = hipGetLastError();
-    if (e == hipSuccess) *riding = true;
+    if (e == hipSuccess) *riding = ride;
     return e;
 }
-
 }  // namespace hcms
