@@ -212,14 +212,14 @@ inline double form_rounds(SplitForm f, int64_t t, int n_cu) {
     if (f.ways == 3) return 0.65 + 0.6 * std::max(0.0, x - 0.59);
     return 0.73 + 0.65 * std::max(0.0, x - 0.59);
 }
-inline double round_us(int nkb) { return 1.65 * nkb + 4.0; }
+inline double round_us(int nkb) { return 1.65 * nkb + 20.0; }
 
 // The split of a launch that copies could ride in, and whether they do.
 // Copies that ride take no time of their own, but a tail shared by more
 // workgroups leaves them fewer CUs and ends earlier.  Of the forms that fit,
 // riding or not, the one expected to end first.  Fitted to the fused and the
-// serial plan of 85 chunkings of S = 3000 to 37000 (within 2 % of the pass):
-// a copy kernel moves 6.5 TB/s, read and written, and takes 1 us more, an idle
+// serial plan of 144 chunkings of S = 1400 to 37000 (1.3 % of the pass off, rms):
+// a copy kernel moves 9 TB/s, read and written, and takes 2 us more, an idle
 // CU copies 12 GB/s.  Two chunks of 12 heads of S = 3178 take 174 us with
 // whole tiles, 199 with the segments over two rounds that a launch without
 // copies takes.
@@ -237,7 +237,7 @@ inline RidingSplit plan_riding(int64_t W, int nkb, int n_cu, const SplitScratch 
     for (const SplitForm &f : kSplitForms) {
         if (!split_fits(f, t, rem, nkb, n_cu, sp)) continue;
         const double tail = form_rounds(f, t, n_cu) * round_us(nkb);
-        if (first) t_best = tail + 2 * copy_bytes / 6.5e6 + n_copies;   // the copies behind it
+        if (first) t_best = tail + 2 * copy_bytes / 9e6 + 2 * n_copies;   // the copies behind it
         first = false;
         const TailSplit p = split_as(f, W, rem, sp);
         const int64_t idle = idle_cus(p, n_cu);
