@@ -331,7 +331,8 @@ HCMS_API int hcms_plan(int n_chunks, int mode, hcms_op *ops, int cap);
  * 0.33 with 3 t <= n_cu, 0.67 with 2 t <= n_cu, 0.9 where its tiles are shared
  * over two rounds (not in lanes), else 1 (S of fewer than 12 key blocks of 64:
  * 0.67 or 1), and lanes last no less than the whole rounds of either lane's
- * launches; chunks that together fill at most one round need rounds saved * S
+ * launches or, of three chunks or more, than the rounds of chunks 0 and 1
+ * together and the second lane's later ones; chunks that together fill at most one round need rounds saved * S
  * >= 8192 and some of it left.  Otherwise, for d = 128 with bf16 storage,
  * HCMS_MODE_FUSED when some launch, its partial round's tiles shared 3 ways
  * where 3 t <= n_cu and 2 ways where 2 t <= n_cu,

@@ -367,17 +367,21 @@ int hcms::auto_plan(int S, int d, int dtype, const int *sizes, int C, int n_cu, 
     // lanes, 126 serial (S = 32760 {5, 5}: lanes 4.3 ms, fused 4.7).
     // Where the kernel shares the tiles of its partial rounds, what counts is
     // what lanes save after that, and no lane ends before its own launches,
-    // which do not share: {8, 7, 7} of S = 5463, 2.8 rounds in 1.9, takes 348
-    // us in lanes, 396 fused; {7, 7, 7} of S = 3390, three rounds of halves,
-    // 212 and 193; {2, 2, 2, 2} of S = 9610, four of thirds, 483 and 419.  100
-    // chunkings of S = 3000 to 40000 that the rule was not made with take 1.2 %
-    // longer than in the better plan, at worst 11 %.
+    // which do not share, nor, of three chunks or more, the second before the
+    // first two chunks' rounds and its own later ones: {8, 7, 7} of S = 5463, 2.8 rounds in 2, takes
+    // 348 us in lanes, 396 fused; {7, 7, 7} of S = 3390, three rounds of
+    // halves, 212 and 193; {2, 2, 2, 2} of S = 9610, four of thirds, 483 and
+    // 419; {2, 2, 1, 1} of S = 19246, whose first two chunks fill 1.2 rounds,
+    // 1300 and 1030.  275 chunkings of S = 3000 to 40000 take 1.2 % longer than
+    // in the better plan, at worst 11 %.
     // The backward shares none, and its rounds last several times as long.
     const int64_t saved = rounds - (total + slots - 1) / slots;
     const bool shares = !backward && d == 128 && dtype == HCMS_BF16;
     const double pooled = static_cast<double>(total / slots) +
                           hcms::attention_partial_round(total % slots, S, n_cu, true);
-    const double less = shared - std::max(pooled, static_cast<double>(std::max(lane[0], lane[1])));
+    const int64_t first_two = tiles * (sizes[0] + int64_t{sizes[1]}), first_one = tiles * sizes[1];
+    const int64_t second = C < 3 ? 0 : (first_two + slots - 1) / slots + lane[1] - (first_one + slots - 1) / slots;
+    const double less = shared - std::max(pooled, static_cast<double>(std::max(lane[0], std::max(lane[1], second))));
     const int64_t lanes_keys = backward ? 512 : 1536;
     const bool faster = !shares ? saved * S >= lanes_keys
                         : total > slots ? less * S >= 1000 : saved * S >= 8192 && shared > pooled + 0.01;

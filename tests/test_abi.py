@@ -719,6 +719,7 @@ def test_auto_mode_of_short_rounds(lib, S, d, sizes, want):
     (15857, (2, 1, 1, 1), "fused"),     # 0.67 + 3 x 0.33, two launches a lane
     (5114, (4, 4, 3, 3), "fused"),      # 80, 80, 60, 60: 4 x 0.33
     (12024, (4, 4, 3), "fused"),        # 188, 188, 141: no round saved
+    (19246, (2, 2, 1, 1), "fused"),     # 152, 152, 76, 76: the first two fill two rounds, chunk 3 a third
     (12986, (4, 4), "fused"),           # 204 each: 2 x 2 rounds, pooled 4
 ])
 def test_auto_mode_counts_shared_rounds(lib, S, sizes, want):
